@@ -253,7 +253,7 @@ som_status som_bmu2_finalize(const double *norms, int64_t V, int64_t M, const in
  * in IEEE half precision and widened to fp32 only for the accumulation, which
  * halves the bytes each codebook row costs). W holds
  * V*M IEEE binary16 bit patterns, feature-major as above, 2-byte aligned
- * (16-byte alignment and M a multiple of 8 select the vector loads). Every
+ * (rows that start 4-byte aligned, so an even M, read fastest). Every
  * other argument, the workspace and the results are those of the fp32 entry
  * point of the same name: the search on an fp16 codebook returns exactly what
  * the fp32 search returns on the same values widened to fp32 (the widening

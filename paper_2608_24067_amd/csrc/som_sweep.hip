@@ -29,21 +29,28 @@ namespace {
 
 // ----------------------------------------------------------------- sweep
 
+// How a lane reads its part of a codebook row: one vector load per group of G neurons,
+// at a group-aligned address (M a multiple of G and W aligned to a group's bytes) or at
+// any element's address (every other M, and slices of a larger array), or element by
+// element (maps of fewer than G neurons, where a group would leave the row).
+constexpr int kLoadScalar = 0, kLoadAligned = 1, kLoadAny = 2;
+
 // Tiles of 8 with eight neurons per lane keep four waves per SIMD (128 registers): the
 // assembly dispatch of fp16 and real-valued rows would otherwise take up to 133 and
 // lose a wave.
-template <typename E, int TA, int NPL, bool VEC, bool REAL>
+template <typename E, int TA, int NPL, int LD, bool REAL>
 constexpr int sweep_min_waves()
 {
-    return (TA == 8 && NPL == 8 && VEC) ? 4 : 1;
+    return (TA == 8 && NPL == 8 && LD != kLoadScalar) ? 4 : 1;
 }
 
 // Workgroup = 4 waves x one strip (blockIdx.y) of 64*NPL neurons, over groups of
 // group_tiles consecutive tiles (a multiple of 4; groups blockIdx.x, blockIdx.x +
 // gridDim.x, ...); each lane owns NPL neurons, in groups of G (four fp32 values, or
-// min(8, NPL) fp16 ones; see loc below). VEC: M is a multiple of G and W aligned to a
-// group's bytes, so each group is one aligned vector load (16 bytes; 8 for fp16 at four
-// neurons per lane).
+// min(8, NPL) fp16 ones; see loc below), each one vector load (16 bytes; 8 for fp16 at
+// four neurons per lane) unless LD is kLoadScalar. A group that reaches past the row's
+// end is read shifted back to end there; its leading elements are then the group
+// before's and are not ranked.
 // The plan is read defensively (offsets, counts and ids clamped to the workspace
 // and the codebook), so even a workspace the plan never wrote cannot drive an
 // access out of bounds.
@@ -55,8 +62,8 @@ constexpr int sweep_min_waves()
 // each union entry's TA sample values (vals); a set mask bit adds value * weight
 // (one fused multiply-add, fp32) instead of the weight, still in ascending feature
 // order per sample.
-template <typename E, int TA, int NPL, int U, bool VEC, bool TOP2, bool REAL>
-__global__ __launch_bounds__(256, (sweep_min_waves<E, TA, NPL, VEC, REAL>())) void k_sweep(
+template <typename E, int TA, int NPL, int U, int LD, bool TOP2, bool REAL>
+__global__ __launch_bounds__(256, (sweep_min_waves<E, TA, NPL, LD, REAL>())) void k_sweep(
     const E *__restrict__ W, const double *__restrict__ norms, int64_t M, int64_t N, int64_t V, int64_t nnz,
     const uint2 *__restrict__ plan, const int2 *__restrict__ tiles, int64_t n_tiles, u64 *__restrict__ keys,
     float *__restrict__ dots, u64 *__restrict__ keys2, float *__restrict__ dots2, const float *__restrict__ vals,
@@ -73,16 +80,32 @@ __global__ __launch_bounds__(256, (sweep_min_waves<E, TA, NPL, VEC, REAL>())) vo
     // lanes' loads of a group cover one contiguous stretch of the row (1 KiB for fp32
     // and for fp16 at 8 neurons per lane).
     constexpr int G = group_elems<E, NPL>();
+    constexpr bool VEC = LD != kLoadScalar;
     const int lg = lane * G;
     // a lane's part of one codebook row, as stored
     struct Seg {
         typedef E vec __attribute__((ext_vector_type(G)));
+        // the same at an element's alignment: the GPU's vector loads take any address
+        typedef vec any __attribute__((aligned(sizeof(E))));
         union {
             vec v[NPL / G];
             E e[NPL];
         };
     };
     auto loc = [&](int j) { return (j / G) * (64 * G) + lg + (j % G); };
+    // Where element j's group is read from, and by how many elements that lies before its
+    // own start (0 but for the last groups of the last strip; G and more: past the map).
+    auto group_at = [&](int j) { return min(base + loc(j - j % G), Mi - G); };
+    auto shift_of = [&](int j) { return LD == kLoadAny ? base + loc(j - j % G) - group_at(j) : 0; };
+    // element j's neuron within the strip, and whether it is ranked as this element's
+    auto slot_of = [&](int j) { return loc(j) - shift_of(j); };
+    auto ranked = [&](int j) { return LD == kLoadAny ? j % G >= shift_of(j) : base + loc(j) < Mi; };
+    auto load_vec = [&](const E *p) {
+        if constexpr (LD == kLoadAny)
+            return (typename Seg::vec)*reinterpret_cast<const typename Seg::any *>(p);
+        else
+            return *reinterpret_cast<const typename Seg::vec *>(p);
+    };
 
     // fp64 norms, +inf past M (those neurons then never pass the candidate test
     // below); nmax = the largest fp32 norm of the strip.
@@ -90,9 +113,8 @@ __global__ __launch_bounds__(256, (sweep_min_waves<E, TA, NPL, VEC, REAL>())) vo
     float nmax_l = 0.0f;
 #pragma unroll
     for (int j = 0; j < NPL; ++j) {
-        const int i = base + loc(j);
-        nrm[j] = i < Mi ? norms[i] : __builtin_inf();
-        if (i < Mi) nmax_l = fmaxf(nmax_l, (float)nrm[j]);
+        nrm[j] = ranked(j) ? norms[base + slot_of(j)] : __builtin_inf();
+        if (ranked(j)) nmax_l = fmaxf(nmax_l, (float)nrm[j]);
     }
     const float nmax = wave_max_f32(nmax_l);
     const unsigned vmax = (unsigned)(V - 1);
@@ -115,8 +137,7 @@ __global__ __launch_bounds__(256, (sweep_min_waves<E, TA, NPL, VEC, REAL>())) vo
     const char *lrow = nullptr;
     unsigned pitch = 0;
     if constexpr (LROW) {
-        const int g = base + lg;
-        lrow = reinterpret_cast<const char *>(W + (g < Mi ? g : Mi - G));
+        lrow = reinterpret_cast<const char *>(W + group_at(0));
         pitch = (unsigned)Mi * (unsigned)sizeof(E);
         asm volatile("" : "+v"(pitch));
     }
@@ -170,17 +191,14 @@ __global__ __launch_bounds__(256, (sweep_min_waves<E, TA, NPL, VEC, REAL>())) vo
         auto row_load = [&](unsigned id, Seg &seg) {
             if constexpr (LROW) {
                 const unsigned idc = id < vmax ? id : vmax;
-                seg.v[0] = *reinterpret_cast<const typename Seg::vec *>(lrow + (uint64_t)idc * pitch);
+                seg.v[0] = load_vec(reinterpret_cast<const E *>(lrow + (uint64_t)idc * pitch));
                 return;
             }
             // 32 x 32-bit product: ids < 2^31 and M <= 2^20
             const E *r = W + (uint64_t)(id < vmax ? id : vmax) * (uint64_t)(unsigned)Mi;
             if constexpr (VEC) {
 #pragma unroll
-                for (int q = 0; q < NPL / G; ++q) {
-                    const int g = base + loc(q * G);
-                    seg.v[q] = *reinterpret_cast<const typename Seg::vec *>(r + (g < Mi ? g : Mi - G));
-                }
+                for (int q = 0; q < NPL / G; ++q) seg.v[q] = load_vec(r + group_at(q * G));
             } else {
 #pragma unroll
                 for (int j = 0; j < NPL; ++j) {
@@ -362,8 +380,8 @@ __global__ __launch_bounds__(256, (sweep_min_waves<E, TA, NPL, VEC, REAL>())) vo
                 float bdot = 0.0f;
                 auto visit = [&](int j, bool cand) {
                     const double d = fma(-2.0, (double)acc[s][j], nrm[j]);
-                    const bool take = cand && base + loc(j) < Mi;
-                    const u64 key = take ? rank_key(d, (unsigned)loc(j)) : kKeyNone;
+                    const bool take = cand && ranked(j);
+                    const u64 key = take ? rank_key(d, (unsigned)slot_of(j)) : kKeyNone;
                     if (key < best) {
                         best = key;
                         bdot = acc[s][j];
@@ -415,8 +433,8 @@ __global__ __launch_bounds__(256, (sweep_min_waves<E, TA, NPL, VEC, REAL>())) vo
                 float q1 = 0.0f, q2 = 0.0f;
                 auto visit = [&](int j, bool cand) {
                     const double d = fma(-2.0, (double)acc[s][j], nrm[j]);
-                    const bool take = cand && base + loc(j) < Mi;
-                    const u64 key = take ? rank_key(d, (unsigned)loc(j)) : kKeyNone;
+                    const bool take = cand && ranked(j);
+                    const u64 key = take ? rank_key(d, (unsigned)slot_of(j)) : kKeyNone;
                     if (key < k1) {
                         k2 = k1;
                         q2 = q1;
@@ -505,8 +523,22 @@ __global__ __launch_bounds__(256, (sweep_min_waves<E, TA, NPL, VEC, REAL>())) vo
 
 // --------------------------------------------------------------- launcher
 
+// The row loads' kind: see kLoadScalar and its siblings. Rows whose starts are only
+// element-aligned were read element by element before, eight loads of 2 or 4 bytes per
+// lane and row: 75 x 75 map, fp32, 30,011 rows 1,227 -> 267 us (266 with M = 5,624);
+// 255 x 255, fp16, 150,001 rows 67.6 -> 12.9 ms. fp32 rows and fp16 rows of even M read as
+// fast as aligned ones (the hardware splits nothing at 4-byte alignment; fp16 M = 65,026:
+// 10.7 ms, 65,024: 10.4); fp16 rows of odd M pay 20% for the odd-addressed half of them.
+template <typename E, int NPL>
+static int row_load_kind(const E *W, int64_t M)
+{
+    constexpr int G = group_elems<E, NPL>();
+    if (M % G == 0 && (reinterpret_cast<uintptr_t>(W) % (G * sizeof(E))) == 0) return kLoadAligned;
+    return M >= G ? kLoadAny : kLoadScalar;
+}
+
 template <typename E, int TA, int NPL, bool TOP2, bool REAL>
-static void sweep_ta(bool vec, dim3 grid, int64_t group_tiles, hipStream_t st, const E *W, const double *norms,
+static void sweep_ta(dim3 grid, int64_t group_tiles, hipStream_t st, const E *W, const double *norms,
                      int64_t M, int64_t N, int64_t V, int64_t nnz, const uint2 *plan, const int2 *tiles, int64_t nt,
                      const SweepOut &o, const float *vals)
 {
@@ -515,12 +547,15 @@ static void sweep_ta(bool vec, dim3 grid, int64_t group_tiles, hipStream_t st, c
     // Tiles of 16 with fp32 rows of four neurons per lane: four registers a row, eight in
     // flight (tiles of 32 keep four: their 128 accumulators leave no room).
     constexpr int UV = (sizeof(E) == 2 && NPL == 8) ? (REAL ? 6 : 8) : (sizeof(E) == 4 && TA == 16 ? 8 : 4);
-    if (vec)
-        hipLaunchKernelGGL((k_sweep<E, TA, NPL, UV, true, TOP2, REAL>), grid, dim3(256), 0, st, W, norms, M, N, V, nnz,
-                           plan, tiles, nt, o.keys, o.dots, o.keys2, o.dots2, vals, group_tiles);
-    else
-        hipLaunchKernelGGL((k_sweep<E, TA, NPL, 4, false, TOP2, REAL>), grid, dim3(256), 0, st, W, norms, M, N, V, nnz,
-                           plan, tiles, nt, o.keys, o.dots, o.keys2, o.dots2, vals, group_tiles);
+    auto launch = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, grid, dim3(256), 0, st, W, norms, M, N, V, nnz, plan, tiles, nt, o.keys, o.dots,
+                           o.keys2, o.dots2, vals, group_tiles);
+    };
+    switch (row_load_kind<E, NPL>(W, M)) {
+    case kLoadAligned: launch(k_sweep<E, TA, NPL, UV, kLoadAligned, TOP2, REAL>); break;
+    case kLoadAny: launch(k_sweep<E, TA, NPL, UV, kLoadAny, TOP2, REAL>); break;
+    default: launch(k_sweep<E, TA, NPL, 4, kLoadScalar, TOP2, REAL>); break;
+    }
 }
 
 // Consecutive tiles per sweep workgroup. Longer groups let a wave keep its strip's
@@ -539,14 +574,6 @@ static int64_t sweep_group_tiles(int64_t nt)
     return g < 4 ? 4 : (g > 32 ? 32 : g);
 }
 
-// Vector loads need M to be a multiple of the group and W aligned to the group's bytes.
-template <typename E, int NPL>
-static bool vector_loads(const E *W, int64_t M)
-{
-    constexpr int G = group_elems<E, NPL>();
-    return M % G == 0 && (reinterpret_cast<uintptr_t>(W) % (G * sizeof(E))) == 0;
-}
-
 template <typename E, bool TOP2>
 static hipError_t sweep_any(int ta, const E *W, const double *norms, int64_t M, int64_t N, int64_t V, int64_t nnz,
                             const uint2 *plan, const int2 *tiles, const float *vals, const SweepOut &o,
@@ -559,21 +586,21 @@ static hipError_t sweep_any(int ta, const E *W, const double *norms, int64_t M, 
     const dim3 grid((unsigned)gx, (unsigned)n_strips(M, ta));
     if (vals) {  // real-valued rows: tiles of 8 only (8 values per plan entry in scalar registers)
         if (ta != 8) return hipErrorInvalidValue;
-        sweep_ta<E, 8, 8, TOP2, true>(vector_loads<E, 8>(W, M), grid, gt, st, W, norms, M, N, V, nnz, plan, tiles,
+        sweep_ta<E, 8, 8, TOP2, true>(grid, gt, st, W, norms, M, N, V, nnz, plan, tiles,
                                       nt, o, vals);
         return hipGetLastError();
     }
     switch (ta) {
     case 8:
-        sweep_ta<E, 8, 8, TOP2, false>(vector_loads<E, 8>(W, M), grid, gt, st, W, norms, M, N, V, nnz, plan, tiles,
+        sweep_ta<E, 8, 8, TOP2, false>(grid, gt, st, W, norms, M, N, V, nnz, plan, tiles,
                                        nt, o, nullptr);
         break;
     case 16:
-        sweep_ta<E, 16, 4, TOP2, false>(vector_loads<E, 4>(W, M), grid, gt, st, W, norms, M, N, V, nnz, plan, tiles,
+        sweep_ta<E, 16, 4, TOP2, false>(grid, gt, st, W, norms, M, N, V, nnz, plan, tiles,
                                         nt, o, nullptr);
         break;
     case 32:
-        sweep_ta<E, 32, 4, TOP2, false>(vector_loads<E, 4>(W, M), grid, gt, st, W, norms, M, N, V, nnz, plan, tiles,
+        sweep_ta<E, 32, 4, TOP2, false>(grid, gt, st, W, norms, M, N, V, nnz, plan, tiles,
                                         nt, o, nullptr);
         break;
     default: return hipErrorInvalidValue;
