@@ -83,8 +83,8 @@ typedef enum {
  * in-range but unspecified results. Row pointers are checked before any row
  * is read: a batch whose row_ptr decreases or leaves [row_ptr[0],
  * row_ptr[0] + nnz] is searched as if every row were empty (each sample gets
- * the unit of smallest norm, lowest index first; its distance is unspecified
- * when the batch is not regrouped), so overlapping rows cannot multiply the
+ * the unit of smallest norm, lowest index first, and that norm as its
+ * distance), so overlapping rows cannot multiply the
  * work. No input drives an access out of bounds. */
 #define SOM_FLAG_ID_RANGE 0x1u   /* a feature id outside [0, V) was skipped      */
 #define SOM_FLAG_UNSORTED 0x2u   /* a row's ids were not strictly ascending       */
@@ -96,7 +96,8 @@ typedef enum {
  * its BMU and distance do not depend on the tile it lands in.
  *   tile_samples  samples per tile, TA (SpMM-tile kernel section): 8, 16 or
  *                 32; 0 selects SOM_DEFAULT_TILE_SAMPLES.
- *   keep_order    0 (default): the plan first regroups the batch by each
+ *   keep_order    0 (default): where it pays (large batches on maps of more
+ *                 than 512 units), the plan first regroups the batch by each
  *                 sample's least frequent feature (the post-submission
  *                 section's lever of clustering samples so tiles share
  *                 features), which shrinks tile unions and keeps rare
@@ -180,7 +181,7 @@ som_status som_bmu_search_noalloc(const float *W, const double *norms, int64_t V
  * left in the same workspace, so they must run in this order on one stream.
  *
  * som_bmu_plan -- tile plan (Algorithm 2, step 5; SpMM-tile kernel section):
- *   unless keep_order is set, the batch is first regrouped by each sample's
+ *   unless keep_order is set, a large batch is first regrouped by each sample's
  *   least frequent feature (a permutation and its row offsets in the workspace;
  *   the rows are read from row_ptr / col_idx through it); then, for each
  *   tile of tile_samples consecutive rows, the ascending list of the distinct

@@ -110,6 +110,7 @@ som_status carve(void *ws, size_t bytes, int64_t N, int64_t M, int64_t V, int64_
     c->out.keys2 = k.layout_top2() ? reinterpret_cast<unsigned long long *>(b + L.keys2) : nullptr;
     c->out.dots2 = k.layout_top2() ? reinterpret_cast<float *>(b + L.dots2) : nullptr;
     c->flags = reinterpret_cast<uint32_t *>(b + L.flags);
+    c->out.flags = c->flags;
     c->ob.freq = reinterpret_cast<uint32_t *>(b + L.freq);
     c->ob.bucket = reinterpret_cast<unsigned long long *>(b + L.bucket);
     c->ob.skey = reinterpret_cast<int32_t *>(b + L.skey);
@@ -186,15 +187,14 @@ som_status plan_impl(const int32_t *row_ptr, const int32_t *col_idx, const float
     if ((st = setup(N, M, V, nnz, config, workspace, workspace_bytes, k, &o, &c, &noop)) != SOM_OK) return st;
     if (noop) return ok();
     hipStream_t s = static_cast<hipStream_t>(stream);
-    hipError_t e = som::launch_clear_flags(c.flags, s);
+    hipError_t e = som::launch_check_rows(row_ptr, N, nnz, c.flags, s);
     if (e != hipSuccess) return hip_fail(e, who);
-    e = som::launch_check_rows(row_ptr, N, nnz, c.flags, s);
-    if (e != hipSuccess) return hip_fail(e, who);
-    if (o.order) {
+    const bool order = o.order && som::regroup_pays(N, M);
+    if (order) {
         e = som::launch_order(row_ptr, col_idx, N, nnz, V, c.ob, c.flags, s);
         if (e != hipSuccess) return hip_fail(e, who);
     }
-    e = som::launch_plan(o.ta, row_ptr, col_idx, k.real ? values : nullptr, N, nnz, V, o.order ? &c.ob : nullptr,
+    e = som::launch_plan(o.ta, row_ptr, col_idx, k.real ? values : nullptr, N, nnz, V, order ? &c.ob : nullptr,
                          c.plan, c.tiles, c.vals, c.xsq, c.flags, s);
     if (e != hipSuccess) return hip_fail(e, who);
     return ok();
@@ -234,8 +234,9 @@ som_status finalize_impl(const Kind &k, const double *norms, int64_t V, int64_t 
         return fail(SOM_ERR_INVALID_ARG, "%s: null pointer", who);
     if ((st = setup(N, M, V, nnz, config, workspace, workspace_bytes, k, &o, &c, &noop)) != SOM_OK) return st;
     if (noop) return ok();
-    hipError_t e = som::launch_finalize(o.ta, norms, M, row_ptr, N, nnz, o.order ? &c.ob : nullptr, c.xsq, c.out, bmu, dist,
-                                        k.top2 ? bmu2 : nullptr, k.top2 ? dist2 : nullptr,
+    const bool order = o.order && som::regroup_pays(N, M);  // as the plan decided
+    hipError_t e = som::launch_finalize(o.ta, norms, M, row_ptr, N, nnz, order ? &c.ob : nullptr, c.xsq, c.out, bmu,
+                                        dist, k.top2 ? bmu2 : nullptr, k.top2 ? dist2 : nullptr,
                                         static_cast<hipStream_t>(stream));
     if (e != hipSuccess) return hip_fail(e, who);
     return ok();

@@ -21,6 +21,17 @@ inline int64_t strip_neurons(int ta) { return 64 * neurons_per_lane(ta); }
 inline int64_t n_strips(int64_t M, int ta) { return (M + strip_neurons(ta) - 1) / strip_neurons(ta); }
 inline int64_t n_tiles(int64_t N, int ta) { return (N + ta - 1) / ta; }
 
+// Whether regrouping a batch by rarest features pays (its caller allowing it). Six kernels
+// and the scattered reads they cause cost 35-45 us and 0.2 ns a row; the sweep then reads
+// rare rows from L2 more often, 1% faster at 16,000 rows and 18-21% at 2,000,000 (fp32;
+// 4-6% for fp16), where the strips do not fit there anyway. Whole searches, fp32, V = 30,000,
+// regrouped / as given: 64 x 64 map 316 / 289 us at 32,000 rows, 521 / 521 at 64,000, 909 /
+// 976 at 128,000; 256 x 256 777 / 738 at 4,000, 1,272 / 1,255 at 8,000, 2,200 / 2,236 at
+// 16,000; 32 x 32 511 / 511 at 256,000; a map of one strip never gains (16 x 16: 1,620 /
+// 1,466 at 2,000,000). fp16 sweeps gain less and break even at two to four times the rows,
+// within 4%; the plan does not know the codebook's type.
+inline bool regroup_pays(int64_t N, int64_t M) { return M > 512 && N >= 8192 && N * M >= (int64_t)1 << 28; }
+
 // One position's result of a regrouped batch, staged in the workspace: a whole 16-byte
 // record, so the finalize writes full lines and the move back to input order reads one
 // record per sample.
@@ -105,6 +116,7 @@ struct SweepOut {
     float *dots;
     unsigned long long *keys2;  // two-best only, else null
     float *dots2;
+    const uint32_t *flags;  // the plan's input flags: a batch with bad row pointers has empty rows
 };
 
 // Records the calling thread's error text (som_last_error) and returns st.
@@ -114,9 +126,8 @@ som_status set_error(som_status st, const char *fmt, ...) __attribute__((format(
 hipError_t launch_norms(const float *W, int64_t V, int64_t M, double *norms, hipStream_t st);
 // fp16 codebooks: W holds IEEE binary16 bit patterns.
 hipError_t launch_norms_f16(const uint16_t *W, int64_t V, int64_t M, double *norms, hipStream_t st);
-hipError_t launch_clear_flags(uint32_t *flags, hipStream_t st);
-// Flags SOM_FLAG_ROW_PTR when row_ptr decreases or leaves [row_ptr[0], row_ptr[0] + nnz];
-// the plan then reads the batch as empty.
+// Clears the flags, then sets SOM_FLAG_ROW_PTR if row_ptr decreases or leaves
+// [row_ptr[0], row_ptr[0] + nnz]; the plan then reads the batch as empty.
 hipError_t launch_check_rows(const int32_t *row_ptr, int64_t N, int64_t nnz, uint32_t *flags, hipStream_t st);
 // values, vals, xsq: real-valued rows only (else null). row_ptr, col_idx, values: the caller's batch.
 // ob non-null: the batch was regrouped: position p's row has plan offsets ob->pos[2p] ... and its

@@ -469,8 +469,7 @@ hipError_t launch_update(bool f16, void *W, int64_t V, int64_t E, const int32_t 
 {
     const int64_t M = E * E;
     // row pointers checked before any row is read: a batch that fails updates nothing
-    hipError_t e = launch_clear_flags(ub.flags, st);
-    if (e == hipSuccess) e = launch_check_rows(row_ptr, N, nnz, ub.flags, st);
+    hipError_t e = launch_check_rows(row_ptr, N, nnz, ub.flags, st);
     if (e != hipSuccess) return e;
     // den: counts, blur, kept in ub.den_blur; the samples of heavy units sorted by unit
     const unsigned sg = (unsigned)((N + 255) / 256 < kScanBlocks ? (N + 255) / 256 + 1 : kScanBlocks);

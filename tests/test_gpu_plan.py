@@ -1,0 +1,100 @@
+"""GPU parity of the tile plan at the sizes where its two forms meet.
+
+Tiles of 8 are planned by ranks while they hold at most 512 ids, by a merge beyond that
+and wherever an id is invalid; batches whose mean tile is long take the merge as a whole.
+The rows here put tiles on both sides of those lines, with empty rows, rows of one id,
+identical rows and a ragged last tile; k/256 weights and values make every distance
+exact, so units and distances are compared with the oracle bit for bit.
+"""
+import numpy as np
+import pytest
+
+import paper_2608_24067_amd.som as som
+import synth
+from parity import compare, compare2, compare_sf, gpu_run, gpu_run2, gpu_run_sf, to_dev
+
+pytestmark = pytest.mark.gpu
+
+V, M = 700, 600
+
+
+def rows_of(lengths, seed, same=False):
+    rng = np.random.default_rng(seed)
+    pick = [np.sort(rng.choice(V, n, replace=False)) for n in lengths]
+    if same:
+        pick = [pick[0]] * len(pick)
+    rp = np.zeros(len(pick) + 1, dtype=np.int32)
+    rp[1:] = np.cumsum([len(p) for p in pick])
+    return rp, np.concatenate(pick).astype(np.int32)
+
+
+CASES = {
+    "tile of 512 ids": [64] * 8 + [3] * 40,
+    "tile of 513 ids": [64] * 7 + [65] + [3] * 40,
+    "one row of 512": [0] * 3 + [512] + [0] * 4 + [5] * 33,
+    "last row holds all": [0] * 7 + [511] + [5] * 33,
+    "one row of 600": [600] + [0] * 7 + [1] * 33,
+    "128 and 129 ids": [16] * 8 + [16] * 7 + [17] + [1] * 9,
+    "64 ids and 65": [8] * 8 + [8] * 7 + [9],
+    "mean at the line": [32] * 64,
+    "mean past the line": [33] * 64,
+    "empty": [0] * 19,
+    "one row": [12],
+}
+
+
+@pytest.mark.parametrize("keep", [False, True])
+@pytest.mark.parametrize("same", [False, True])
+@pytest.mark.parametrize("name", CASES)
+def test_plan_forms(dev, name, same, keep):
+    rp, ci = rows_of(CASES[name], len(name), same and CASES[name][0] > 0)
+    W = synth.codebook(500, synth.QUANTISED, V, M)
+    b, d, _ = gpu_run(W, rp, ci, dev, keep_order=keep)
+    compare(W, rp, ci, b, d, exact=True, what=name)
+    vals = synth.values(500, len(ci), synth.VAL_QUANTISED)
+    compare_sf(W, rp, ci, vals, gpu_run_sf(W, rp, ci, vals, dev, keep_order=keep), exact=True, what=name)
+
+
+@pytest.mark.parametrize("how", ["past V", "negative", "repeated", "descending"])
+def test_invalid_ids_in_a_short_tile_are_flagged_and_stay_local(dev, how):
+    rp, ci = rows_of([12] * 24, 7)
+    bad = ci.copy()
+    at = int(rp[9]) + 5
+    bad[at] = {"past V": V, "negative": -1, "repeated": ci[at - 1], "descending": ci[at - 2]}[how]
+    W = synth.codebook(501, synth.QUANTISED, V, M)
+    Wd, rpd = to_dev(W, dev), to_dev(rp, dev)
+    norms = som.codebook_norms(Wd, V, M)
+    ws = som.alloc_workspace(24, M, V, len(ci), dev, keep_order=True)
+    b, d = (t.cpu().numpy() for t in som.bmu_search(Wd, norms, rpd, to_dev(ci, dev), V, M, nnz=len(ci), workspace=ws,
+                                                    keep_order=True))
+    assert som.input_flags(ws, 24, M, V, len(ci), keep_order=True) == 0
+    b2, d2 = (t.cpu().numpy() for t in som.bmu_search(Wd, norms, rpd, to_dev(bad, dev), V, M, nnz=len(ci),
+                                                      workspace=ws, keep_order=True))
+    want = som.FLAG_ID_RANGE if how in ("past V", "negative") else som.FLAG_UNSORTED
+    assert som.input_flags(ws, 24, M, V, len(ci), keep_order=True) == want
+    others = np.arange(24) != 9
+    assert np.array_equal(b[others], b2[others]) and np.array_equal(d[others], d2[others])
+    assert (b2 >= 0).all() and (b2 < M).all()
+
+
+@pytest.mark.parametrize("vocabulary", [3, 8193, 32769, 70001])
+def test_regrouped_batch_equals_the_given_order(dev, vocabulary):
+    # 263,000 rows on 1,024 units are regrouped: feature counts in LDS (both sizes) and in
+    # global memory, the bucket scan in one and in several steps, its last words ragged
+    import torch
+
+    N, units = 263_000, 1024
+    rp, ci = synth.make_csr(31, N, vocabulary, lam=2.0 if vocabulary == 3 else 6.0)
+    g = torch.Generator(device=dev).manual_seed(5)
+    W = torch.rand((vocabulary, units), device=dev, generator=g)
+    given = gpu_run2(W, rp, ci, dev, keep_order=True)
+    for a, b in zip(gpu_run2(W, rp, ci, dev), given):
+        assert np.array_equal(a, b)
+    bad = rp.copy()
+    bad[N // 2] = -5  # row pointers that leave the batch: every row reads as empty, whatever the order
+    norms = som.codebook_norms(W, vocabulary, units)
+    best = int(torch.argmin(norms))
+    for keep in (False, True):
+        b, d = som.bmu_search(W, norms, to_dev(bad, dev), to_dev(ci, dev), vocabulary, units, nnz=len(ci),
+                              keep_order=keep)
+        assert bool((b == best).all()) and bool((d == norms[best]).all())
