@@ -8,7 +8,8 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libsom.so")
-SOURCES = [os.path.join(CSRC, "som_sweep.hip"), os.path.join(CSRC, "som_kernels.hip"), os.path.join(CSRC, "som_update.hip"),
+SOURCES = [os.path.join(CSRC, "som_sweep.hip"), os.path.join(CSRC, "som_rows.hip"),
+           os.path.join(CSRC, "som_kernels.hip"), os.path.join(CSRC, "som_update.hip"),
            os.path.join(CSRC, "som_api.cpp"), os.path.join(CSRC, "som_noalloc.hip")]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")

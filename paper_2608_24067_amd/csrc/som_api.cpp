@@ -111,6 +111,7 @@ som_status carve(void *ws, size_t bytes, int64_t N, int64_t M, int64_t V, int64_
     c->out.dots2 = k.layout_top2() ? reinterpret_cast<float *>(b + L.dots2) : nullptr;
     c->flags = reinterpret_cast<uint32_t *>(b + L.flags);
     c->out.flags = c->flags;
+    c->out.direct = nullptr;
     c->ob.freq = reinterpret_cast<uint32_t *>(b + L.freq);
     c->ob.bucket = reinterpret_cast<unsigned long long *>(b + L.bucket);
     c->ob.skey = reinterpret_cast<int32_t *>(b + L.skey);
@@ -258,6 +259,19 @@ som_status search_impl(const Book &b, const Kind &k, const double *norms, int64_
     if ((st = check_book(b, who)) != SOM_OK) return st;
     if ((st = setup(N, M, V, nnz, config, workspace, workspace_bytes, k, &o, &c, &noop)) != SOM_OK) return st;
     if (noop) return ok();
+    if (som::rows_direct(N, M, o.ta)) {
+        // the tile table's section holds a byte per row
+        const som::DirectRows d{row_ptr, col_idx, values, c.xsq, reinterpret_cast<uint8_t *>(c.tiles), c.flags};
+        som::SweepOut out = c.out;
+        out.direct = &d;
+        hipStream_t s = static_cast<hipStream_t>(stream);
+        hipError_t e = som::launch_sweep(8, b.f16, k.top2, b.p, norms, M, N, V, nnz, nullptr, nullptr, nullptr, out, s);
+        if (e != hipSuccess) return hip_fail(e, who);
+        e = som::launch_finalize(8, norms, M, row_ptr, N, nnz, nullptr, c.xsq, out, bmu, dist,
+                                 k.top2 ? bmu2 : nullptr, k.top2 ? dist2 : nullptr, s);
+        if (e != hipSuccess) return hip_fail(e, who);
+        return ok();
+    }
     if ((st = plan_impl(row_ptr, col_idx, values, N, nnz, V, M, workspace, workspace_bytes, config, stream, k, who)) !=
         SOM_OK)
         return st;

@@ -36,6 +36,12 @@ __host__ __device__ constexpr int group_elems()
     return (int)(16 / sizeof(E)) < NPL ? (int)(16 / sizeof(E)) : NPL;
 }
 
+// How a lane reads its part of a codebook row: one vector load per group of G neurons,
+// at a group-aligned address (M a multiple of G and W aligned to a group's bytes) or at
+// any element's address (every other M, and slices of a larger array), or element by
+// element (maps of fewer than G neurons, where a group would leave the row).
+constexpr int kLoadScalar = 0, kLoadAligned = 1, kLoadAny = 2;
+
 // GRP consecutive elements at p (aligned to GRP * sizeof(E) bytes) as floats.
 template <typename E, int GRP>
 __device__ __forceinline__ void load_group(const E *p, float *w)
@@ -261,6 +267,13 @@ __device__ __forceinline__ int64_t csr_base(const int32_t *row_ptr, int64_t &nnz
         return 0;
     }
     return b;
+}
+
+// Whether row s's pointers decrease or leave [base, base + nnz].
+__device__ __forceinline__ bool row_bad(const int32_t *row_ptr, int64_t base, int64_t nnz, int64_t s)
+{
+    const int64_t a = (int64_t)row_ptr[s] - base, b = (int64_t)row_ptr[s + 1] - base;
+    return b < a || a < 0 || b > nnz;
 }
 
 }  // namespace

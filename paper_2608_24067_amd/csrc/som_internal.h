@@ -32,6 +32,18 @@ inline int64_t n_tiles(int64_t N, int ta) { return (N + ta - 1) / ta; }
 // within 4%; the plan does not know the codebook's type.
 inline bool regroup_pays(int64_t N, int64_t M) { return M > 512 && N >= 8192 && N * M >= (int64_t)1 << 28; }
 
+// Whether a search reads its rows without a plan (som_rows.hip). That saves two launches and
+// the walk over tiles' unions, and reads a codebook row once per sample instead of once per
+// tile: it wins while the rows times the units are few. Without / with the plan, us, fp32:
+// 64 x 64 map 13.8 / 27 at one row, 15 / 36 at 512, 23 / 37 at 1,024, 44 / 44 at 2,048;
+// 256 x 256 28 / 43 at 64, 88 / 101 at 256, 165 / 161 at 512; 512 x 512 61 / 86 at 33,
+// 114 / 114 at 64 (fp16: 62 / 67). The rows' flags take a byte each in the tile table's
+// section, which holds a byte per row at tiles of 8 and 256 at any tile size.
+inline bool rows_direct(int64_t N, int64_t M, int ta)
+{
+    return (N <= 256 && N * M <= (int64_t)1 << 24) || (N <= 1024 && ta == 8 && N * M <= (int64_t)1 << 23);
+}
+
 // One position's result of a regrouped batch, staged in the workspace: a whole 16-byte
 // record, so the finalize writes full lines and the move back to input order reads one
 // record per sample.
@@ -110,6 +122,16 @@ struct OrderBuffers {
     Staged *res, *res2;  // results by position (res2: two-best only)
 };
 
+// A few rows searched without a plan (som_rows.hip): the caller's batch, and what the
+// sweep leaves for the finalize besides the keys.
+struct DirectRows {
+    const int32_t *row_ptr, *col_idx;
+    const float *values;
+    double *xsq;         // double [N]: ||x||^2 of real-valued rows (else null)
+    uint8_t *row_flags;  // uint8 [N]: each row's input flags
+    uint32_t *flags;     // the workspace's input flags, which the finalize writes
+};
+
 // Where the sweep leaves its per-(sample, strip) results.
 struct SweepOut {
     unsigned long long *keys;
@@ -117,6 +139,7 @@ struct SweepOut {
     unsigned long long *keys2;  // two-best only, else null
     float *dots2;
     const uint32_t *flags;  // the plan's input flags: a batch with bad row pointers has empty rows
+    const DirectRows *direct;  // non-null: rows searched without a plan
 };
 
 // Records the calling thread's error text (som_last_error) and returns st.
@@ -139,6 +162,9 @@ hipError_t launch_plan(int ta, const int32_t *row_ptr, const int32_t *col_idx, c
 hipError_t launch_sweep(int ta, bool f16, bool top2, const void *W, const double *norms, int64_t M, int64_t N,
                         int64_t V, int64_t nnz, const uint2 *plan, const int2 *tiles, const float *vals,
                         const SweepOut &o, hipStream_t st);
+// The sweep of rows without a plan (o.direct), on strips of 512 neurons.
+hipError_t launch_rows(bool f16, bool top2, const void *W, const double *norms, int64_t M, int64_t N, int64_t V,
+                       int64_t nnz, const SweepOut &o, hipStream_t st);
 // bmu2/dist2 non-null: the two best units. xsq: real-valued rows (else ||x||^2 = nnz of the row).
 // ob non-null: the batch was regrouped (the row lengths come from ob->pos, not row_ptr); results
 // are staged by position and then moved to their samples.

@@ -62,12 +62,6 @@ __global__ void k_clear_flags(uint32_t *flags) { flags[threadIdx.x] = 0u; }
 // so row pointers that decrease cannot make rows overlap and multiply the work.
 // The flags start from zero: cleared by k_clear_flags, or by k_check_few where one
 // workgroup checks the whole batch.
-__device__ __forceinline__ bool row_bad(const int32_t *row_ptr, int64_t base, int64_t nnz, int64_t s)
-{
-    const int64_t a = (int64_t)row_ptr[s] - base, b = (int64_t)row_ptr[s + 1] - base;
-    return b < a || a < 0 || b > nnz;
-}
-
 constexpr int64_t kCheckFew = 8192;  // rows one workgroup checks: eight per thread, one round trip
 
 __global__ __launch_bounds__(1024) void k_check_few(const int32_t *__restrict__ row_ptr, int64_t N, int64_t nnz,
@@ -736,6 +730,28 @@ inline int finalize_waves(int64_t n_strips)
     return (int)w;
 }
 
+// The batch's input flags: the plan's, or, for rows searched without a plan, each row's own
+// (row pointers are judged for the batch, so every row's byte tells), which the first
+// workgroup gathers into the workspace's word.
+struct FinalIn {
+    const uint32_t *flags;
+    const uint8_t *row_flags;  // non-null: no plan
+    uint32_t *gather;
+    __device__ int64_t rows(int64_t N, int64_t nnz) const
+    {
+        if (!row_flags) return rows_nnz(flags, nnz);
+        if (blockIdx.x == 0 && threadIdx.y == 0 && threadIdx.x < 64) {
+            unsigned f = 0;
+#pragma unroll 8
+            for (int64_t s = threadIdx.x; s < N; s += 64) f |= row_flags[s];
+#pragma unroll
+            for (int d = 1; d < 64; d <<= 1) f |= (unsigned)__shfl_xor((int)f, d);
+            gather[threadIdx.x] = threadIdx.x == 0 ? f : 0u;
+        }
+        return (row_flags[0] & SOM_FLAG_ROW_PTR) ? 0 : nnz;
+    }
+};
+
 // Ids of position k's row (0 for a batch whose row pointers were flagged).
 __device__ __forceinline__ double row_length(const int32_t *row_ptr, int rs, int64_t base, int64_t nnz, int64_t k)
 {
@@ -745,13 +761,13 @@ __device__ __forceinline__ double row_length(const int32_t *row_ptr, int rs, int
 
 __global__ __launch_bounds__(64 * kFinalizeWaves) void k_finalize(
     const double *__restrict__ norms, int64_t M, const int32_t *__restrict__ row_ptr, int rs, int64_t N, int64_t nnz,
-    const uint32_t *__restrict__ flags, const double *__restrict__ xsq, const u64 *__restrict__ keys,
+    FinalIn in, const double *__restrict__ xsq, const u64 *__restrict__ keys,
     const float *__restrict__ dots, int64_t n_strips, FinalOut out)
 {
     __shared__ u64 lk[kFinalizeWaves][64];
     __shared__ int ls[kFinalizeWaves][64];
     const int waves = (int)blockDim.y, y = (int)threadIdx.y;
-    nnz = rows_nnz(flags, nnz);
+    nnz = in.rows(N, nnz);
     const int64_t base = csr_base(row_ptr, nnz);
     for (int64_t k0 = (int64_t)blockIdx.x * blockDim.x; k0 < N; k0 += (int64_t)gridDim.x * blockDim.x) {  // uniform
         const int64_t k = k0 + threadIdx.x;
@@ -814,13 +830,13 @@ struct TwoKeys {
 
 __global__ __launch_bounds__(64 * kFinalizeWaves) void k_finalize2(
     const double *__restrict__ norms, int64_t M, const int32_t *__restrict__ row_ptr, int rs, int64_t N, int64_t nnz,
-    const uint32_t *__restrict__ flags, const double *__restrict__ xsq, const u64 *__restrict__ keys,
+    FinalIn in, const double *__restrict__ xsq, const u64 *__restrict__ keys,
     const float *__restrict__ dots, const u64 *__restrict__ keys2, const float *__restrict__ dots2, int64_t n_strips,
     FinalOut out, FinalOut out2)
 {
     __shared__ TwoKeys lds[kFinalizeWaves][64];
     const int waves = (int)blockDim.y, y = (int)threadIdx.y;
-    nnz = rows_nnz(flags, nnz);
+    nnz = in.rows(N, nnz);
     const int64_t base = csr_base(row_ptr, nnz);
     for (int64_t k0 = (int64_t)blockIdx.x * blockDim.x; k0 < N; k0 += (int64_t)gridDim.x * blockDim.x) {  // uniform
         const int64_t k = k0 + threadIdx.x;
@@ -1001,11 +1017,12 @@ hipError_t launch_finalize(int ta, const double *norms, int64_t M, const int32_t
     const FinalOut o1{bmu, dist, ob ? ob->res : nullptr}, o2{bmu2, dist2, ob ? ob->res2 : nullptr};
     const int32_t *rp = ob ? ob->pos : row_ptr;
     const int rs = ob ? 2 : 1;
+    const FinalIn fin{o.flags, o.direct ? o.direct->row_flags : nullptr, o.direct ? o.direct->flags : nullptr};
     if (bmu2)
-        hipLaunchKernelGGL(k_finalize2, dim3((unsigned)blocks), block, 0, st, norms, M, rp, rs, N, nnz, o.flags, xsq,
+        hipLaunchKernelGGL(k_finalize2, dim3((unsigned)blocks), block, 0, st, norms, M, rp, rs, N, nnz, fin, xsq,
                            o.keys, o.dots, o.keys2, o.dots2, ns, o1, o2);
     else
-        hipLaunchKernelGGL(k_finalize, dim3((unsigned)blocks), block, 0, st, norms, M, rp, rs, N, nnz, o.flags, xsq,
+        hipLaunchKernelGGL(k_finalize, dim3((unsigned)blocks), block, 0, st, norms, M, rp, rs, N, nnz, fin, xsq,
                            o.keys, o.dots, ns, o1);
     if (ob) {
         int64_t ub = (N + 255) / 256;

@@ -29,12 +29,6 @@ namespace {
 
 // ----------------------------------------------------------------- sweep
 
-// How a lane reads its part of a codebook row: one vector load per group of G neurons,
-// at a group-aligned address (M a multiple of G and W aligned to a group's bytes) or at
-// any element's address (every other M, and slices of a larger array), or element by
-// element (maps of fewer than G neurons, where a group would leave the row).
-constexpr int kLoadScalar = 0, kLoadAligned = 1, kLoadAny = 2;
-
 // Tiles of 8 with eight neurons per lane keep four waves per SIMD (128 registers): the
 // assembly dispatch of fp16 and real-valued rows would otherwise take up to 133 and
 // lose a wave.
@@ -612,6 +606,7 @@ hipError_t launch_sweep(int ta, bool f16, bool top2, const void *W, const double
                         int64_t V, int64_t nnz, const uint2 *plan, const int2 *tiles, const float *vals,
                         const SweepOut &o, hipStream_t st)
 {
+    if (o.direct) return launch_rows(f16, top2, W, norms, M, N, V, nnz, o, st);
     if (f16) {
         const _Float16 *w = static_cast<const _Float16 *>(W);
         return top2 ? sweep_any<_Float16, true>(ta, w, norms, M, N, V, nnz, plan, tiles, vals, o, st)

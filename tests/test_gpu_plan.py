@@ -11,7 +11,8 @@ import pytest
 
 import paper_2608_24067_amd.som as som
 import synth
-from parity import compare, compare2, compare_sf, gpu_run, gpu_run2, gpu_run_sf, to_dev
+from parity import compare, compare_sf, gpu_run2, to_dev
+from test_gpu_row_loads import phases
 
 pytestmark = pytest.mark.gpu
 
@@ -43,16 +44,15 @@ CASES = {
 }
 
 
-@pytest.mark.parametrize("keep", [False, True])
 @pytest.mark.parametrize("same", [False, True])
 @pytest.mark.parametrize("name", CASES)
-def test_plan_forms(dev, name, same, keep):
+def test_plan_forms(dev, name, same):
     rp, ci = rows_of(CASES[name], len(name), same and CASES[name][0] > 0)
     W = synth.codebook(500, synth.QUANTISED, V, M)
-    b, d, _ = gpu_run(W, rp, ci, dev, keep_order=keep)
-    compare(W, rp, ci, b, d, exact=True, what=name)
+    Wd = to_dev(W, dev)
+    compare(W, rp, ci, *phases(Wd, rp, ci, dev, 8, False), exact=True, what=name)
     vals = synth.values(500, len(ci), synth.VAL_QUANTISED)
-    compare_sf(W, rp, ci, vals, gpu_run_sf(W, rp, ci, vals, dev, keep_order=keep), exact=True, what=name)
+    compare_sf(W, rp, ci, vals, phases(Wd, rp, ci, dev, 8, True, vals), exact=True, what=name)
 
 
 @pytest.mark.parametrize("how", ["past V", "negative", "repeated", "descending"])
@@ -65,11 +65,17 @@ def test_invalid_ids_in_a_short_tile_are_flagged_and_stay_local(dev, how):
     Wd, rpd = to_dev(W, dev), to_dev(rp, dev)
     norms = som.codebook_norms(Wd, V, M)
     ws = som.alloc_workspace(24, M, V, len(ci), dev, keep_order=True)
-    b, d = (t.cpu().numpy() for t in som.bmu_search(Wd, norms, rpd, to_dev(ci, dev), V, M, nnz=len(ci), workspace=ws,
-                                                    keep_order=True))
+
+    def run(ids):
+        b, d = to_dev(np.empty(24, np.int32), dev), to_dev(np.empty(24), dev)
+        som.bmu_plan(rpd, to_dev(ids, dev), V, M, len(ci), ws, keep_order=True)
+        som.bmu_sweep(Wd, norms, V, M, 24, len(ci), ws, keep_order=True)
+        som.bmu_finalize(norms, rpd, V, M, len(ci), b, d, ws, keep_order=True)
+        return b.cpu().numpy(), d.cpu().numpy()
+
+    b, d = run(ci)
     assert som.input_flags(ws, 24, M, V, len(ci), keep_order=True) == 0
-    b2, d2 = (t.cpu().numpy() for t in som.bmu_search(Wd, norms, rpd, to_dev(bad, dev), V, M, nnz=len(ci),
-                                                      workspace=ws, keep_order=True))
+    b2, d2 = run(bad)
     want = som.FLAG_ID_RANGE if how in ("past V", "negative") else som.FLAG_UNSORTED
     assert som.input_flags(ws, 24, M, V, len(ci), keep_order=True) == want
     others = np.arange(24) != 9

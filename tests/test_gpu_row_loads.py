@@ -12,11 +12,36 @@ import pytest
 import torch
 
 import synth
-from parity import compare, compare2, compare_sf, gpu_run, gpu_run2, gpu_run_sf
+import paper_2608_24067_amd.som as som
+from parity import compare, compare2, compare_sf, to_dev
 
 pytestmark = pytest.mark.gpu
 
 N, V = 75, 60
+
+
+def phases(W, rp, ci, dev, tile, two, values=None):
+    """The search in its phases, which always take the planned sweep (a whole search of few rows does not)."""
+    V, M = W.shape
+    N, nnz = len(rp) - 1, len(ci)
+    rp, ci = to_dev(rp, dev), to_dev(ci, dev)
+    norms = som.codebook_norms(W, V, M)
+    out = tuple(torch.empty(N, dtype=t, device=dev) for t in ((torch.int32, torch.float64) * (2 if two else 1)))
+    if values is not None:
+        ws = som.alloc_workspace_sf(N, M, V, nnz, dev)
+        som.bmu_sf_plan(rp, ci, to_dev(values, dev), V, M, nnz, ws)
+        som.bmu_sf_sweep(W, norms, V, M, N, nnz, ws, two_best=two)
+        som.bmu_sf_finalize(norms, rp, V, M, nnz, out, ws)
+    else:
+        ws = som.alloc_workspace2(N, M, V, nnz, dev, tile_samples=tile)
+        som.bmu_plan(rp, ci, V, M, nnz, ws, tile_samples=tile)
+        if two:
+            som.bmu2_sweep(W, norms, V, M, N, nnz, ws, tile_samples=tile)
+            som.bmu2_finalize(norms, rp, V, M, nnz, out, ws, tile_samples=tile)
+        else:
+            som.bmu_sweep(W, norms, V, M, N, nnz, ws, tile_samples=tile)
+            som.bmu_finalize(norms, rp, V, M, nnz, *out, ws, tile_samples=tile)
+    return tuple(t.cpu().numpy() for t in out)
 
 
 @pytest.mark.parametrize("tile", [8, 16, 32])
@@ -31,12 +56,11 @@ def test_any_width_and_start(dev, M, start, dtype, tile):
     flat[start:].copy_(torch.from_numpy(W.reshape(-1)))
     view = flat[start:].view(V, M)
     what = f"M={M} start={start} {dtype} TA={tile}"
-    b, d, _ = gpu_run(view, rp, ci, dev, tile_samples=tile)
-    compare(W, rp, ci, b, d, exact=True, what=what)
-    compare2(W, rp, ci, gpu_run2(view, rp, ci, dev, tile_samples=tile), exact=True, what=what)
+    compare(W, rp, ci, *phases(view, rp, ci, dev, tile, False), exact=True, what=what)
+    compare2(W, rp, ci, phases(view, rp, ci, dev, tile, True), exact=True, what=what)
     if tile == 8:
         vals = synth.values(400 + M, len(ci), synth.VAL_QUANTISED)
-        compare_sf(W, rp, ci, vals, gpu_run_sf(view, rp, ci, vals, dev), exact=True, what=what + " real")
+        compare_sf(W, rp, ci, vals, phases(view, rp, ci, dev, 8, True, vals), exact=True, what=what + " real")
 
 
 def test_overflowing_norms_rank_only_owned_neurons(dev):
@@ -47,5 +71,5 @@ def test_overflowing_norms_rank_only_owned_neurons(dev):
     W = np.full((V2, M), 3e19, dtype=np.float32)  # norms overflow fp32, not fp64
     W[:, 513] = 1.0
     W[:, 514] = 2.0
-    g = gpu_run2(W, rp, ci, dev)
+    g = phases(to_dev(W, dev), rp, ci, dev, 8, True)
     assert (g[0] == 513).all() and (g[2] == 514).all()
