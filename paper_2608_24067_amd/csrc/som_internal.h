@@ -37,11 +37,14 @@ inline bool regroup_pays(int64_t N, int64_t M) { return M > 512 && N >= 8192 && 
 // tile: it wins while the rows times the units are few. Without / with the plan, us, fp32:
 // 64 x 64 map 13.8 / 27 at one row, 15 / 36 at 512, 23 / 37 at 1,024, 44 / 44 at 2,048;
 // 256 x 256 28 / 43 at 64, 88 / 101 at 256, 165 / 161 at 512; 512 x 512 61 / 86 at 33,
-// 114 / 114 at 64 (fp16: 62 / 67). The rows' flags take a byte each in the tile table's
+// 114 / 114 at 64 (fp16: 62 / 67); 16 x 16 map 14 / 33 at 2,048, 22 / 33 at 4,096; 32 x 32 19 /
+// 36 at 2,048, 36 / 37 at 4,096. The rows' flags take a byte each in the tile table's
 // section, which holds a byte per row at tiles of 8 and 256 at any tile size.
 inline bool rows_direct(int64_t N, int64_t M, int ta)
 {
-    return (N <= 256 && N * M <= (int64_t)1 << 24) || (N <= 1024 && ta == 8 && N * M <= (int64_t)1 << 23);
+    const int64_t pairs = N * M;
+    return (N <= 256 && pairs <= (int64_t)1 << 24) ||
+           (ta == 8 && ((N <= 1024 && pairs <= (int64_t)1 << 23) || (N <= 4096 && pairs <= (int64_t)3 << 20)));
 }
 
 // One position's result of a regrouped batch, staged in the workspace: a whole 16-byte

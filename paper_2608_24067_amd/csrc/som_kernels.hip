@@ -20,12 +20,11 @@ namespace {
 
 // n_i = sum_v W[v*M+i]^2: one thread per neuron, v ascending, fp64. The square of
 // an fp32 (or fp16) value is exact in fp64, so fma(w, w, acc) equals acc + w*w.
-// One wave per workgroup, so a small map (M = 4096: 64 waves) still spreads over
-// 64 compute units, and NL rows in flight per wave: the sums are sequential, the
-// loads are not. A map of fewer than kNormWavesFew waves is bound by each lane's
-// chain of batches, so it takes 128 rows per batch (64x64 map: 0.64 -> 0.45 ms);
-// larger maps keep 32 (128 costs 10% at 256x256, where 32 already reads at 7 TB/s).
-constexpr int kNormWavesFew = 512;
+// One wave per workgroup and NL rows in flight per wave: the sums are sequential, the
+// loads are not. 32 rows read at 7 TB/s on a 256 x 256 map, where 128 cost 10%; a map of
+// fewer than kNormWavesFew waves is bound by each lane's chain of batches and takes 128
+// (130 x 130 map 785 -> 608 us).
+constexpr int64_t kNormWavesFew = 512;
 
 template <typename E, int NL>
 __global__ __launch_bounds__(64) void k_norms(const E *__restrict__ W, int64_t V, int64_t M,
@@ -54,6 +53,79 @@ __global__ __launch_bounds__(64) void k_norms(const E *__restrict__ W, int64_t V
     norms[i] = acc;
 }
 
+// The same for a map of no more waves than compute units, where each lane's chain of load
+// batches was the time (64 x 64: 0.44 ms for 0.5 GB). Seven waves of a workgroup bring the
+// rows of its 64 neurons, kNormDepth chunks of kNormRows rows each in flight, and leave
+// their squares (exact in fp64) in LDS; the eighth adds them up in ascending v, one dependent
+// fp64 addition per row, while the others fill the other half: V additions of about 10 ns
+// are the bound. V = 30,000, fp32: 64 x 64 436 -> 328 us, 128 x 128 490 -> 343; fp16 549 -> 337.
+constexpr int kNormProducers = 7, kNormRows = 16, kNormDepth = 3;
+constexpr int kNormChunk = kNormProducers * kNormRows;
+constexpr int64_t kNormFewBlocks = 256;
+
+template <typename E>
+__global__ __launch_bounds__(64 * (kNormProducers + 1)) void k_norms_few(const E *__restrict__ W, int64_t V, int64_t M,
+                                                                         double *__restrict__ norms)
+{
+    __shared__ double sq[2][kNormChunk][64];
+    const int lane = threadIdx.x & 63, w = wave_id();
+    const int64_t i = (int64_t)blockIdx.x * 64 + lane;
+    const int64_t chunks = (V + kNormChunk - 1) / kNormChunk;
+    if (w == 0) {
+        double acc = 0.0;
+        for (int64_t c = 0; c < chunks; ++c) {
+            __syncthreads();
+            const double(*s)[64] = sq[c & 1];
+            // a batch of squares is read while the one before it is added
+            double x[2][kNormRows];
+#pragma unroll
+            for (int u = 0; u < kNormRows; ++u) x[0][u] = s[u][lane];
+#pragma unroll
+            for (int b = 0; b < kNormProducers; ++b) {
+                if (b + 1 < kNormProducers)
+#pragma unroll
+                    for (int u = 0; u < kNormRows; ++u) x[(b + 1) & 1][u] = s[(b + 1) * kNormRows + u][lane];
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int u = 0; u < kNormRows; ++u) acc += x[b & 1][u];
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+        if (i < M) norms[i] = acc;
+        return;
+    }
+    const unsigned col = (unsigned)(i < M ? i : M - 1);  // beside a row's uniform address
+    E x[kNormDepth][kNormRows];
+    auto load = [&](int64_t c, E *to) {
+        // rows past V read the last one (a branch here would make the waits below wait for
+        // the newest loads) and add +0, which leaves a sum of squares as it is
+        const int64_t v0 = c * kNormChunk + (w - 1) * kNormRows;
+#pragma unroll
+        for (int u = 0; u < kNormRows; ++u)
+            to[u] = __builtin_nontemporal_load(W + (v0 + u < V ? v0 + u : V - 1) * M + col);
+    };
+#pragma unroll
+    for (int d = 0; d < kNormDepth; ++d) load(d, x[d]);
+    for (int64_t c0 = 0; c0 < chunks; c0 += kNormDepth) {
+#pragma unroll
+        for (int d = 0; d < kNormDepth; ++d) {
+            const int64_t c = c0 + d;
+            if (c >= chunks) break;  // uniform over the workgroup, as for the eighth wave
+            double(*s)[64] = sq[c & 1] + (w - 1) * kNormRows;
+#pragma unroll
+            for (int u = 0; u < kNormRows; ++u) {
+                const double q = (double)(float)x[d][u];
+                s[u][lane] = q * q;
+            }
+            if ((c + 1) * kNormChunk > V)  // uniform
+                for (int u = 0; u < kNormRows; ++u)
+                    if (c * kNormChunk + (w - 1) * kNormRows + u >= V) s[u][lane] = 0.0;
+            load(c + kNormDepth, x[d]);
+            __syncthreads();
+        }
+    }
+}
+
 __global__ void k_clear_flags(uint32_t *flags) { flags[threadIdx.x] = 0u; }
 
 // Row pointers checked before any kernel walks a row: non-decreasing and inside
@@ -62,7 +134,9 @@ __global__ void k_clear_flags(uint32_t *flags) { flags[threadIdx.x] = 0u; }
 // so row pointers that decrease cannot make rows overlap and multiply the work.
 // The flags start from zero: cleared by k_clear_flags, or by k_check_few where one
 // workgroup checks the whole batch.
-constexpr int64_t kCheckFew = 8192;  // rows one workgroup checks: eight per thread, one round trip
+// Rows one workgroup checks, eight per thread in one round trip (at 10,000 rows the search is
+// 2 us slower so than with two launches).
+constexpr int64_t kCheckFew = 8192;
 
 __global__ __launch_bounds__(1024) void k_check_few(const int32_t *__restrict__ row_ptr, int64_t N, int64_t nnz,
                                                     uint32_t *__restrict__ flags)
@@ -915,25 +989,28 @@ __global__ __launch_bounds__(256) void k_unpermute(const int32_t *__restrict__ i
 
 // --------------------------------------------------------------- launchers
 
-hipError_t launch_norms(const float *W, int64_t V, int64_t M, double *norms, hipStream_t st)
+template <typename E>
+static hipError_t norms_any(const E *W, int64_t V, int64_t M, double *norms, hipStream_t st)
 {
     const int64_t blocks = (M + 63) / 64;
-    if (blocks < kNormWavesFew)
-        hipLaunchKernelGGL((k_norms<float, 128>), dim3((unsigned)blocks), dim3(64), 0, st, W, V, M, norms);
+    if (blocks <= kNormFewBlocks)
+        hipLaunchKernelGGL(k_norms_few<E>, dim3((unsigned)blocks), dim3(64 * (kNormProducers + 1)), 0, st, W, V, M,
+                           norms);
+    else if (blocks < kNormWavesFew)
+        hipLaunchKernelGGL((k_norms<E, 128>), dim3((unsigned)blocks), dim3(64), 0, st, W, V, M, norms);
     else
-        hipLaunchKernelGGL((k_norms<float, 32>), dim3((unsigned)blocks), dim3(64), 0, st, W, V, M, norms);
+        hipLaunchKernelGGL((k_norms<E, 32>), dim3((unsigned)blocks), dim3(64), 0, st, W, V, M, norms);
     return hipGetLastError();
+}
+
+hipError_t launch_norms(const float *W, int64_t V, int64_t M, double *norms, hipStream_t st)
+{
+    return norms_any(W, V, M, norms, st);
 }
 
 hipError_t launch_norms_f16(const uint16_t *W, int64_t V, int64_t M, double *norms, hipStream_t st)
 {
-    const int64_t blocks = (M + 63) / 64;
-    const _Float16 *w = reinterpret_cast<const _Float16 *>(W);
-    if (blocks < kNormWavesFew)
-        hipLaunchKernelGGL((k_norms<_Float16, 128>), dim3((unsigned)blocks), dim3(64), 0, st, w, V, M, norms);
-    else
-        hipLaunchKernelGGL((k_norms<_Float16, 32>), dim3((unsigned)blocks), dim3(64), 0, st, w, V, M, norms);
-    return hipGetLastError();
+    return norms_any(reinterpret_cast<const _Float16 *>(W), V, M, norms, st);
 }
 
 hipError_t launch_check_rows(const int32_t *row_ptr, int64_t N, int64_t nnz, uint32_t *flags, hipStream_t st)

@@ -60,7 +60,7 @@ def both_paths(W, rp, ci, V, M, two, values=None, nnz=None):
 
 @pytest.mark.parametrize("dtype", [torch.float32, torch.float16])
 @pytest.mark.parametrize("M", [1, 3, 5, 8, 511, 513, 1500, 2047])
-@pytest.mark.parametrize("N", [1, 65, 256, 1024, 1025])
+@pytest.mark.parametrize("N", [1, 65, 256, 1024, 1025, 4096])
 def test_equals_phases_and_oracle(dev, N, M, dtype):
     rp, ci = batch(N, 10 * N + M)
     W = synth.codebook(600 + M, synth.QUANTISED, V, M)
