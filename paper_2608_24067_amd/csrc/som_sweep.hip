@@ -101,16 +101,13 @@ __global__ __launch_bounds__(256, (sweep_min_waves<E, TA, NPL, LD, REAL>())) voi
             return *reinterpret_cast<const typename Seg::vec *>(p);
     };
 
-    // fp64 norms, +inf past M (those neurons then never pass the candidate test
-    // below); nmax = the largest fp32 norm of the strip.
+    // fp64 norms, +inf past M (those neurons then never pass the candidate test below). They
+    // are first used in the epilogue of the wave's first tile, so their way from memory is
+    // hidden behind that tile's rows.
     double nrm[NPL];
-    float nmax_l = 0.0f;
 #pragma unroll
-    for (int j = 0; j < NPL; ++j) {
-        nrm[j] = ranked(j) ? norms[base + slot_of(j)] : __builtin_inf();
-        if (ranked(j)) nmax_l = fmaxf(nmax_l, (float)nrm[j]);
-    }
-    const float nmax = wave_max_f32(nmax_l);
+    for (int j = 0; j < NPL; ++j) nrm[j] = ranked(j) ? norms[base + slot_of(j)] : __builtin_inf();
+    float nmax = -1.0f;  // the largest fp32 norm of the strip, once known
     const unsigned vmax = (unsigned)(V - 1);
     // Tiles of 16 with four fp32 neurons per lane: the row dispatch is one assembly
     // block per row (som_tree16.h), and a row's address is one vector multiply-add
@@ -346,6 +343,13 @@ __global__ __launch_bounds__(256, (sweep_min_waves<E, TA, NPL, LD, REAL>())) voi
             asm volatile("" : "+v"(x));
             nf[j] = (float)x;
         }
+        if (nmax < 0.0f) {  // uniform
+            float nmax_l = 0.0f;
+#pragma unroll
+            for (int j = 0; j < NPL; ++j)
+                if (ranked(j)) nmax_l = fmaxf(nmax_l, nf[j]);
+            nmax = wave_max_f32(nmax_l);
+        }
         u64 mine = kKeyNone, mine2 = kKeyNone;
         float mine_dot = 0.0f, mine_dot2 = 0.0f;
 #pragma unroll
@@ -554,18 +558,26 @@ static void sweep_ta(dim3 grid, int64_t group_tiles, hipStream_t st, const E *W,
 
 // Consecutive tiles per sweep workgroup. Longer groups let a wave keep its strip's
 // norms over several tiles and keep the tiles in flight a compact stretch of the
-// (regrouped) batch, but a strip must still span many rounds of resident
-// workgroups, or the chip works on two strips at once and their rows compete for
-// L2: up to 32 tiles, and at least 16,384 groups per strip where there are enough.
-// From 60,000 tiles on, groups hold at least 8 tiles (two per wave): the 1024 x 1024
-// map's 500,000 rows (62,500 tiles) then still span 7,800 groups, about seven rounds,
-// per strip, and the sweep takes 769 ms instead of 784; 12 or 16 tiles (5,200 or
-// 3,900 groups) cost 4-7%.
-static int64_t sweep_group_tiles(int64_t nt)
+// (regrouped) batch, but a strip must still span enough rounds of resident workgroups, or
+// the chip works on two strips at once and their rows compete for L2.
+// fp32: 8 tiles from 12,000 on, then one in 10,240, up to 32 (V = 20,000, ms by group size: 64 x 64, 31,250 tiles 1.48 at 4, 1.43 at 8 and 12, 1.50 at 32;
+// 128 x 128, 15,000 tiles 2.86, 2.82, 2.87, 3.36; 256 x 256, 7,500 tiles 6.12, 6.22, 6.54,
+// 8.52; 1024 x 1024, 62,500 tiles 784, 769, 812, 835).
+// fp16 rows are half as long, so two strips at once still fit and the tile's prologue and
+// neighbourhood count for more: 8 tiles from 1,500 on, 12 from 6,000, 16 from 12,000, 24 from
+// 20,000, 32 from 30,000 (256 x 256: 2,000 tiles 1.24 at 4, 1.20 at 8, 1.50 at 32; 7,500 tiles
+// 4.23, 4.01, 3.92; 25,000 tiles 13.46, 12.62, 11.99; 1024 x 1024, 62,500 tiles 552, 520, 491).
+// Tiles of 16 and 32 keep the line they were measured with.
+static int64_t sweep_group_tiles(int64_t nt, int ta, bool f16)
 {
-    int64_t g = nt / 16384 / 4 * 4;
-    if (g < 8 && nt >= 8 * 7500) g = 8;
-    return g < 4 ? 4 : (g > 32 ? 32 : g);
+    if (ta != 8) {
+        int64_t g = nt / 16384 / 4 * 4;
+        if (g < 8 && nt >= 8 * 7500) g = 8;
+        return g < 4 ? 4 : (g > 32 ? 32 : g);
+    }
+    if (f16) return nt >= 30000 ? 32 : nt >= 20000 ? 24 : nt >= 12000 ? 16 : nt >= 6000 ? 12 : nt >= 1500 ? 8 : 4;
+    const int64_t g = nt / 10240 / 4 * 4, least = nt >= 12000 ? 8 : 4;
+    return g < least ? least : (g > 32 ? 32 : g);
 }
 
 template <typename E, bool TOP2>
@@ -574,7 +586,7 @@ static hipError_t sweep_any(int ta, const E *W, const double *norms, int64_t M, 
                             hipStream_t st)
 {
     const int64_t nt = n_tiles(N, ta);
-    const int64_t gt = sweep_group_tiles(nt);
+    const int64_t gt = sweep_group_tiles(nt, ta, sizeof(E) == 2);
     int64_t gx = (nt + gt - 1) / gt;
     if (gx > (1 << 20)) gx = 1 << 20;
     const dim3 grid((unsigned)gx, (unsigned)n_strips(M, ta));
