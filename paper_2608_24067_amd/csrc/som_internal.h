@@ -186,7 +186,7 @@ hipError_t launch_order(const int32_t *row_ptr, const int32_t *col_idx, int64_t 
 struct UpdateBuffers {
     uint32_t *flags;  // SOM_FLAG_ROW_PTR: the batch's row pointers are invalid, nothing is updated
     int32_t *den_cnt;
-    int32_t *sup_row, *sup;  // the exact support of the blurred den (row windows, then both axes)
+    int32_t *sup_row, *sup;  // occupied units in reach along the row (the column windows need no buffer: sup is free)
     float *den_a, *den_b;  // scratch of the den blur
     float *den_blur;       // the blurred den
     int32_t *start, *cursor, *slot, *hunit, *order;
