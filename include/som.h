@@ -148,9 +148,9 @@ som_status som_codebook_norms(const float *W, int64_t V, int64_t M, double *norm
  *   workspace  device, >= som_bmu_workspace_bytes(N, M, V, nnz, config)
  *              bytes, 256-byte aligned; its contents are scratch.
  *   config     NULL or a som_bmu_config (host memory, read during the call).
- * The results are those of som_bmu_plan, som_bmu_sweep, som_bmu_finalize in
- * order; a search of few rows computes them without a plan, so the workspace
- * it leaves holds none for a later phase call.
+ * Equivalent to som_bmu_plan, som_bmu_sweep, som_bmu_finalize in order: the
+ * workspace it leaves serves later phase calls (a sweep of another codebook
+ * over the same batch, say).
  */
 som_status som_bmu_search(const float *W, const double *norms, int64_t V, int64_t M, const int32_t *row_ptr,
                           const int32_t *col_idx, int64_t N, int64_t nnz, int32_t *bmu, double *dist,

@@ -260,14 +260,13 @@ som_status search_impl(const Book &b, const Kind &k, const double *norms, int64_
     if ((st = setup(N, M, V, nnz, config, workspace, workspace_bytes, k, &o, &c, &noop)) != SOM_OK) return st;
     if (noop) return ok();
     if (som::rows_direct(N, M, o.ta)) {
-        // the tile table's section holds a byte per row
-        const som::DirectRows d{row_ptr, col_idx, values, c.xsq, reinterpret_cast<uint8_t *>(c.tiles), c.flags};
+        const som::DirectRows d{row_ptr, col_idx, values, o.ta, c.plan, c.tiles, c.vals, c.xsq, c.flags};
         som::SweepOut out = c.out;
         out.direct = &d;
         hipStream_t s = static_cast<hipStream_t>(stream);
-        hipError_t e = som::launch_sweep(8, b.f16, k.top2, b.p, norms, M, N, V, nnz, nullptr, nullptr, nullptr, out, s);
+        hipError_t e = som::launch_sweep(o.ta, b.f16, k.top2, b.p, norms, M, N, V, nnz, nullptr, nullptr, nullptr, out, s);
         if (e != hipSuccess) return hip_fail(e, who);
-        e = som::launch_finalize(8, norms, M, row_ptr, N, nnz, nullptr, c.xsq, out, bmu, dist,
+        e = som::launch_finalize(o.ta, norms, M, row_ptr, N, nnz, nullptr, c.xsq, out, bmu, dist,
                                  k.top2 ? bmu2 : nullptr, k.top2 ? dist2 : nullptr, s);
         if (e != hipSuccess) return hip_fail(e, who);
         return ok();

@@ -86,6 +86,20 @@ __device__ __forceinline__ unsigned plan_word(unsigned mask)
         return mask;
 }
 
+// The second word of an entry held by sample `slot` alone at tiles of ta samples, or of one
+// held by none (an id outside [0, V)).
+__device__ __forceinline__ unsigned plan_word_one(int ta, int slot, bool held)
+{
+    if (ta == 32) return held ? 1u << slot : 0u;
+    return held ? plan_word<16>(1u << slot) : kPlanMulti;
+}
+
+// Rows searched without a plan pass each row's input flags on in the key of strip 0, whose
+// index field (below 512 there) leaves these bits free.
+constexpr int kKeyFlagShift = 17;
+constexpr u64 kKeyFlags = 7ull << kKeyFlagShift;
+static_assert((SOM_FLAG_ID_RANGE | SOM_FLAG_UNSORTED | SOM_FLAG_ROW_PTR) == 7u, "three flags");
+
 // The sample mask of a plan word.
 template <int TA>
 __device__ __forceinline__ unsigned plan_mask(unsigned y)

@@ -16,7 +16,7 @@ inline bool valid_tile(int ta) { return ta == 8 || ta == 16 || ta == 32; }
 // Neurons per lane of the sweep: 8 (two 16-byte loads per codebook row) for tiles of 8
 // samples, 4 for larger tiles, so that the TA x NPL register accumulators stay at
 // 64 or 128 VGPRs. One wave covers a strip of 64 * NPL neurons.
-inline int neurons_per_lane(int ta) { return ta <= 8 ? 8 : 4; }
+constexpr int neurons_per_lane(int ta) { return ta <= 8 ? 8 : 4; }
 inline int64_t strip_neurons(int ta) { return 64 * neurons_per_lane(ta); }
 inline int64_t n_strips(int64_t M, int ta) { return (M + strip_neurons(ta) - 1) / strip_neurons(ta); }
 inline int64_t n_tiles(int64_t N, int ta) { return (N + ta - 1) / ta; }
@@ -38,8 +38,7 @@ inline bool regroup_pays(int64_t N, int64_t M) { return M > 512 && N >= 8192 && 
 // 64 x 64 map 13.8 / 27 at one row, 15 / 36 at 512, 23 / 37 at 1,024, 44 / 44 at 2,048;
 // 256 x 256 28 / 43 at 64, 88 / 101 at 256, 165 / 161 at 512; 512 x 512 61 / 86 at 33,
 // 114 / 114 at 64 (fp16: 62 / 67); 16 x 16 map 14 / 33 at 2,048, 22 / 33 at 4,096; 32 x 32 19 /
-// 36 at 2,048, 36 / 37 at 4,096. The rows' flags take a byte each in the tile table's
-// section, which holds a byte per row at tiles of 8 and 256 at any tile size.
+// 36 at 2,048, 36 / 37 at 4,096.
 inline bool rows_direct(int64_t N, int64_t M, int ta)
 {
     const int64_t pairs = N * M;
@@ -126,13 +125,16 @@ struct OrderBuffers {
 };
 
 // A few rows searched without a plan (som_rows.hip): the caller's batch, and what the
-// sweep leaves for the finalize besides the keys.
+// sweep leaves besides the keys: ||x||^2, and the plan for a later phase call.
 struct DirectRows {
     const int32_t *row_ptr, *col_idx;
     const float *values;
-    double *xsq;         // double [N]: ||x||^2 of real-valued rows (else null)
-    uint8_t *row_flags;  // uint8 [N]: each row's input flags
-    uint32_t *flags;     // the workspace's input flags, which the finalize writes
+    int ta;           // samples per tile of the plan
+    uint2 *plan;
+    int2 *tiles;
+    float *vals;      // real-valued rows only, as xsq (else null)
+    double *xsq;
+    uint32_t *flags;  // the workspace's input flags, which the finalize writes
 };
 
 // Where the sweep leaves its per-(sample, strip) results.
@@ -165,7 +167,7 @@ hipError_t launch_plan(int ta, const int32_t *row_ptr, const int32_t *col_idx, c
 hipError_t launch_sweep(int ta, bool f16, bool top2, const void *W, const double *norms, int64_t M, int64_t N,
                         int64_t V, int64_t nnz, const uint2 *plan, const int2 *tiles, const float *vals,
                         const SweepOut &o, hipStream_t st);
-// The sweep of rows without a plan (o.direct), on strips of 512 neurons.
+// The sweep of rows without a plan (o.direct).
 hipError_t launch_rows(bool f16, bool top2, const void *W, const double *norms, int64_t M, int64_t N, int64_t V,
                        int64_t nnz, const SweepOut &o, hipStream_t st);
 // bmu2/dist2 non-null: the two best units. xsq: real-valued rows (else ||x||^2 = nnz of the row).

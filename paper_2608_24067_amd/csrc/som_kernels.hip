@@ -805,24 +805,25 @@ inline int finalize_waves(int64_t n_strips)
 }
 
 // The batch's input flags: the plan's, or, for rows searched without a plan, each row's own
-// (row pointers are judged for the batch, so every row's byte tells), which the first
+// (row pointers are judged for the batch, so every row's key tells), which the first
 // workgroup gathers into the workspace's word.
 struct FinalIn {
     const uint32_t *flags;
-    const uint8_t *row_flags;  // non-null: no plan
+    const u64 *row_keys;  // non-null: no plan; the keys of strip 0
     uint32_t *gather;
+    static __device__ unsigned flags_of(u64 key) { return (unsigned)((key & kKeyFlags) >> kKeyFlagShift); }
     __device__ int64_t rows(int64_t N, int64_t nnz) const
     {
-        if (!row_flags) return rows_nnz(flags, nnz);
+        if (!row_keys) return rows_nnz(flags, nnz);
         if (blockIdx.x == 0 && threadIdx.y == 0 && threadIdx.x < 64) {
             unsigned f = 0;
 #pragma unroll 8
-            for (int64_t s = threadIdx.x; s < N; s += 64) f |= row_flags[s];
+            for (int64_t s = threadIdx.x; s < N; s += 64) f |= flags_of(row_keys[s]);
 #pragma unroll
             for (int d = 1; d < 64; d <<= 1) f |= (unsigned)__shfl_xor((int)f, d);
             gather[threadIdx.x] = threadIdx.x == 0 ? f : 0u;
         }
-        return (row_flags[0] & SOM_FLAG_ROW_PTR) ? 0 : nnz;
+        return (flags_of(row_keys[0]) & SOM_FLAG_ROW_PTR) ? 0 : nnz;
     }
 };
 
@@ -854,6 +855,7 @@ __global__ __launch_bounds__(64 * kFinalizeWaves) void k_finalize(
 #pragma unroll
                 for (int j = 0; j < kFinalizeBatch; ++j)
                     kk[j] = g0 + j * waves < n_strips ? keys[(g0 + j * waves) * N + k] : kKeyNone;
+                if (g0 == 0) kk[0] &= ~kKeyFlags;  // the flags that strip 0's key may carry
 #pragma unroll
                 for (int j = 0; j < kFinalizeBatch; ++j)
                     if (kk[j] < best) {
@@ -929,6 +931,7 @@ __global__ __launch_bounds__(64 * kFinalizeWaves) void k_finalize2(
                     k2[j] = in ? keys2[at] : kKeyNone;
                     d2[j] = in ? dots2[at] : 0.0f;
                 }
+                if (g0 == 0) k1[0] &= ~kKeyFlags;  // the flags that strip 0's key may carry
 #pragma unroll
                 for (int j = 0; j < kFinalize2Batch; ++j) {
                     t.offer(k1[j], d1[j]);
@@ -1094,7 +1097,7 @@ hipError_t launch_finalize(int ta, const double *norms, int64_t M, const int32_t
     const FinalOut o1{bmu, dist, ob ? ob->res : nullptr}, o2{bmu2, dist2, ob ? ob->res2 : nullptr};
     const int32_t *rp = ob ? ob->pos : row_ptr;
     const int rs = ob ? 2 : 1;
-    const FinalIn fin{o.flags, o.direct ? o.direct->row_flags : nullptr, o.direct ? o.direct->flags : nullptr};
+    const FinalIn fin{o.flags, o.direct ? o.keys : nullptr, o.direct ? o.direct->flags : nullptr};
     if (bmu2)
         hipLaunchKernelGGL(k_finalize2, dim3((unsigned)blocks), block, 0, st, norms, M, rp, rs, N, nnz, fin, xsq,
                            o.keys, o.dots, o.keys2, o.dots2, ns, o1, o2);

@@ -11,24 +11,29 @@
 // The result is the planned sweep's, bit for bit: the same fp32 sum in the row's order,
 // the same two-stage ranking (an fp32 bound, then fp64 keys of the neurons within it; see
 // k_sweep for the bound), one key and dot product per row and strip.
+//
+// The waves of strip 0 also leave a plan in the workspace, as a search with a plan would: a
+// tile's entries are its rows' ids one row after the other, each held by its own sample
+// alone. It is longer than a merged one where rows share features, and a sweep of it adds
+// every sample's weights in the same order.
 
 #include "som_device.h"
 
 namespace som {
 namespace {
 
-constexpr int kNpl = 8;  // neurons per lane: strips of 512, as the workspace's keys are laid out
-
-template <typename E, int LD, bool TOP2, bool REAL>
+// kNpl: neurons per lane, as the workspace's keys are laid out (strips of 64 kNpl)
+template <typename E, int kNpl, int LD, bool TOP2, bool REAL>
 __global__ __launch_bounds__(64) void k_rows(const E *__restrict__ W, const double *__restrict__ norms, int64_t M,
                                              int64_t N, int64_t V, int64_t nnz, const int32_t *__restrict__ row_ptr,
                                              const int32_t *__restrict__ col_idx, const float *__restrict__ values,
                                              u64 *__restrict__ keys, float *__restrict__ dots,
                                              u64 *__restrict__ keys2, float *__restrict__ dots2,
-                                             double *__restrict__ xsq, uint8_t *__restrict__ row_flags)
+                                             double *__restrict__ xsq, int ta, uint2 *__restrict__ plan,
+                                             int2 *__restrict__ tiles, float *__restrict__ vals)
 {
     constexpr int G = group_elems<E, kNpl>();
-    constexpr int U = sizeof(E) == 2 ? 16 : 8;  // codebook rows in flight: 64 registers
+    constexpr int U = kNpl * sizeof(E) == 32 ? 8 : 16;  // codebook rows in flight: up to 64 registers
     typedef E vec __attribute__((ext_vector_type(G)));
     typedef vec any __attribute__((aligned(sizeof(E))));
     const int lane = threadIdx.x;
@@ -49,6 +54,9 @@ __global__ __launch_bounds__(64) void k_rows(const E *__restrict__ W, const doub
     for (int64_t s = lane; s < N; s += 64) bad |= row_bad(row_ptr, first, nnz, s);
     const bool flagged = __ballot(bad) != 0;
     const int64_t rb = flagged ? 0 : row_ptr[row], re = flagged ? 0 : row_ptr[row + 1];
+
+    const int shift = kNpl == 8 ? 3 : (ta == 16 ? 4 : 5);  // 2^shift samples per tile
+    const int slot = (int)row & ((1 << shift) - 1);
 
     double nrm[kNpl];
     float nf[kNpl], nmax_l = 0.0f;
@@ -77,6 +85,11 @@ __global__ __launch_bounds__(64) void k_rows(const E *__restrict__ W, const doub
         const int left = __shfl(id, below ? 63 - __builtin_clzll(below) : 0);
         if (__ballot(in && id <= (below ? left : prev))) flag |= SOM_FLAG_UNSORTED;
         if (valid) prev = __builtin_amdgcn_readlane(id, 63 - __builtin_clzll(valid));
+        if (strip == 0 && lane < n) {
+            const int64_t at = p0 + lane - first;
+            plan[at] = make_uint2((unsigned)id, plan_word_one(1 << shift, slot, in));
+            if constexpr (REAL) vals[(at << shift) + slot] = x;
+        }
         for (int k = 0; k < n; k += U) {
             union {
                 vec v[U][kNpl / G];
@@ -156,7 +169,7 @@ __global__ __launch_bounds__(64) void k_rows(const E *__restrict__ W, const doub
     const int o1 = owner_of(k1, K1);
     const float D1 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(q1), o1));
     if (lane == 0) {
-        keys[strip * N + row] = K1;
+        keys[strip * N + row] = strip == 0 ? (K1 & ~kKeyFlags) | (u64)flag << kKeyFlagShift : K1;
         dots[strip * N + row] = D1;
     }
     if constexpr (TOP2) {
@@ -170,26 +183,29 @@ __global__ __launch_bounds__(64) void k_rows(const E *__restrict__ W, const doub
         }
     }
     if (strip == 0 && lane == 0) {
-        row_flags[row] = (uint8_t)flag;
         if constexpr (REAL) xsq[row] = sq;
+        if (slot == 0) {
+            const int64_t end = row + (1 << shift) < N ? row + (1 << shift) : N;
+            tiles[row >> shift] = flagged ? make_int2(0, 0) : make_int2((int)(rb - first), (int)(row_ptr[end] - rb));
+        }
     }
 }
 
-template <typename E, bool TOP2, bool REAL>
+template <typename E, int NPL, bool TOP2, bool REAL>
 hipError_t rows_any(const void *w, const double *norms, int64_t M, int64_t N, int64_t V, int64_t nnz,
                     const SweepOut &o, hipStream_t st)
 {
     const E *W = static_cast<const E *>(w);
-    const dim3 grid((unsigned)n_strips(M, 8), (unsigned)N);
     const DirectRows &d = *o.direct;
+    const dim3 grid((unsigned)n_strips(M, d.ta), (unsigned)N);
     auto launch = [&](auto kernel) {
         hipLaunchKernelGGL(kernel, grid, dim3(64), 0, st, W, norms, M, N, V, nnz, d.row_ptr, d.col_idx, d.values,
-                           o.keys, o.dots, o.keys2, o.dots2, d.xsq, d.row_flags);
+                           o.keys, o.dots, o.keys2, o.dots2, d.xsq, d.ta, d.plan, d.tiles, d.vals);
     };
-    if (M >= group_elems<E, kNpl>())
-        launch(k_rows<E, kLoadAny, TOP2, REAL>);
+    if (M >= group_elems<E, NPL>())
+        launch(k_rows<E, NPL, kLoadAny, TOP2, REAL>);
     else
-        launch(k_rows<E, kLoadScalar, TOP2, REAL>);
+        launch(k_rows<E, NPL, kLoadScalar, TOP2, REAL>);
     return hipGetLastError();
 }
 
@@ -199,13 +215,19 @@ hipError_t launch_rows(bool f16, bool top2, const void *W, const double *norms, 
                        int64_t nnz, const SweepOut &o, hipStream_t st)
 {
     const bool real = o.direct->xsq != nullptr;
+    if (real && o.direct->ta != 8) return hipErrorInvalidValue;
+    static_assert(neurons_per_lane(8) == 8 && neurons_per_lane(16) == 4 && neurons_per_lane(32) == 4,
+                  "the kernels below");
     auto pick = [&](auto e) {
         typedef decltype(e) E;
         if (real)
-            return top2 ? rows_any<E, true, true>(W, norms, M, N, V, nnz, o, st)
-                        : rows_any<E, false, true>(W, norms, M, N, V, nnz, o, st);
-        return top2 ? rows_any<E, true, false>(W, norms, M, N, V, nnz, o, st)
-                    : rows_any<E, false, false>(W, norms, M, N, V, nnz, o, st);
+            return top2 ? rows_any<E, 8, true, true>(W, norms, M, N, V, nnz, o, st)
+                        : rows_any<E, 8, false, true>(W, norms, M, N, V, nnz, o, st);
+        if (o.direct->ta == 8)
+            return top2 ? rows_any<E, 8, true, false>(W, norms, M, N, V, nnz, o, st)
+                        : rows_any<E, 8, false, false>(W, norms, M, N, V, nnz, o, st);
+        return top2 ? rows_any<E, 4, true, false>(W, norms, M, N, V, nnz, o, st)
+                    : rows_any<E, 4, false, false>(W, norms, M, N, V, nnz, o, st);
     };
     return f16 ? pick(_Float16{}) : pick(float{});
 }

@@ -135,3 +135,66 @@ def test_slice_of_a_larger_batch(dev):
     cut = to_dev(rp[50:91], dev)
     a, fa, b, fb = both_paths(W, cut, to_dev(ci, dev), V, M, False, nnz=int(rp[90] - rp[50]))
     assert fa == fb == 0 and torch.equal(a[0], b[0]) and torch.equal(a[1], b[1])
+
+
+def later_phases(W2, rp, ci, V, M, two, ws, nnz, values=None, **kw):
+    """A sweep of codebook W2 with the plan that a workspace holds, and the finalize."""
+    N = rp.numel() - 1
+    norms = som.codebook_norms(W2, V, M)
+    out = tuple(torch.full((N,), -7, dtype=t, device=W2.device)
+                for t in (torch.int32, torch.float64) * (2 if two else 1))
+    if values is not None:
+        som.bmu_sf_sweep(W2, norms, V, M, N, nnz, ws, two_best=two, **kw)
+        som.bmu_sf_finalize(norms, rp, V, M, nnz, out, ws, **kw)
+    elif two:
+        som.bmu2_sweep(W2, norms, V, M, N, nnz, ws, **kw)
+        som.bmu2_finalize(norms, rp, V, M, nnz, out, ws, **kw)
+    else:
+        som.bmu_sweep(W2, norms, V, M, N, nnz, ws, **kw)
+        som.bmu_finalize(norms, rp, V, M, nnz, out[0], out[1], ws, **kw)
+    return out
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.float16])
+@pytest.mark.parametrize("kind,two,tile", [("binary", False, 8), ("binary", True, 8), ("binary", False, 16),
+                                           ("binary", True, 16), ("binary", False, 32), ("binary", True, 32),
+                                           ("real", False, 8), ("real", True, 8)])
+@pytest.mark.parametrize("N,M,input", [(1, 700, ""), (40, 1030, ""), (250, 3, ""), (45, 515, "bad id"),
+                                       (45, 515, "bad rows")])
+def test_the_search_leaves_its_plan(dev, kind, two, tile, N, M, input, dtype):
+    rp, ci = batch(N, 40 + N)
+    if input == "bad id":
+        ci[int(rp[9]) + 5], ci[int(rp[20])] = V, -1
+    elif input == "bad rows":
+        rp[9] = rp[7]
+    nnz = len(ci)
+    W = [to_dev(synth.codebook(90 + k, synth.UNIFORM, V, M), dev).to(dtype) for k in range(2)]
+    rp, ci = to_dev(rp, dev), to_dev(ci, dev)
+    values = to_dev(synth.values(91, nnz, synth.VAL_QUANTISED), dev) if kind == "real" else None
+    kw = {"tile_samples": tile}
+    ws = (som.alloc_workspace_sf if values is not None else som.alloc_workspace2)(N, M, V, nnz, dev, **kw)
+    norms = som.codebook_norms(W[0], V, M)
+
+    def search(W, norms):
+        if values is not None:
+            return som.bmu_sf_search(W, norms, rp, ci, values, V, M, nnz=nnz, two_best=two, workspace=ws, **kw)
+        return (som.bmu2_search if two else som.bmu_search)(W, norms, rp, ci, V, M, nnz=nnz, workspace=ws, **kw)
+
+    want = search(W[1], som.codebook_norms(W[1], V, M))
+    ws.fill_(0x5A)
+    first = [t.clone() for t in search(W[0], norms)]
+    # the finalize once more, from what the search left
+    again = tuple(torch.full_like(t, -7) for t in first)
+    if values is not None:
+        som.bmu_sf_finalize(norms, rp, V, M, nnz, again, ws, **kw)
+    elif two:
+        som.bmu2_finalize(norms, rp, V, M, nnz, again, ws, **kw)
+    else:
+        som.bmu_finalize(norms, rp, V, M, nnz, again[0], again[1], ws, **kw)
+    flags = som.input_flags(ws, N, M, V, nnz, **kw)
+    got = later_phases(W[1], rp, ci, V, M, two, ws, nnz, values, **kw)
+    assert som.input_flags(ws, N, M, V, nnz, **kw) == flags
+    for a, b in zip(again, first):
+        assert torch.equal(a, b)
+    for a, b in zip(got, want):
+        assert torch.equal(a, b)
