@@ -1016,11 +1016,42 @@ BlurPlan blur_plan(int64_t E, int64_t r)
     return b;
 }
 
-template <typename K>
-void allow_lds(K kernel, size_t bytes)
+// f(StaticInt<R>): the half-width whose windows are held in registers, 0 for none.
+template <typename F>
+auto with_radius(const BlurPlan &b, int64_t r, F &&f)
 {
-    (void)hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
-                              (int)bytes);
+    static_assert(kRegRadius == 8, "the radii below");
+    switch (b.small ? (int)r : 0) {
+    case 1: return f(StaticInt<1>{});
+    case 2: return f(StaticInt<2>{});
+    case 3: return f(StaticInt<3>{});
+    case 4: return f(StaticInt<4>{});
+    case 5: return f(StaticInt<5>{});
+    case 6: return f(StaticInt<6>{});
+    case 7: return f(StaticInt<7>{});
+    case 8: return f(StaticInt<8>{});
+    default: return f(StaticInt<0>{});
+    }
+}
+
+// Lets the kernels of blur_lds take a compute unit's LDS. The limit belongs to the process,
+// so it is the same for every call: a smaller one would take away what another thread's
+// launch of the same kernel is about to use.
+template <typename T, bool DEN>
+hipError_t allow_blur_lds(const BlurPlan &b, int64_t r)
+{
+    auto allow = [](auto kernel) {
+        return hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                   kLdsBytes);
+    };
+    return with_radius(b, r, [&](auto radius) {
+        constexpr int R = decltype(radius)::value;
+        if (b.lattice) return allow(k_lattice<T, DEN, R>);
+        hipError_t e = allow(k_rows3<R>);
+        if constexpr (R == 0)
+            if (e == hipSuccess) e = allow(k_cols3<T, DEN>);
+        return e;
+    });
 }
 
 // The blur of f feature-major lattices of counts and its quotients into W from feature v0
@@ -1032,41 +1063,26 @@ void blur_lds(const BlurPlan &b, const int32_t *cnt, float *rows, T *W, const fl
 {
     const int n = (int)E, rr = (int)(r < E ? r : E);
     auto grid = [](int64_t g) { return dim3((unsigned)(g < (1 << 20) ? g : 1 << 20)); };
-    auto run = [&](auto radius) {
+    with_radius(b, r, [&](auto radius) {
         constexpr int R = decltype(radius)::value;
         const dim3 block(kBlurThreads);
         if (b.lattice) {
             const size_t lds = (size_t)b.lp.words * b.lp.per * 4;
-            allow_lds(k_lattice<T, DEN, R>, lds);
             hipLaunchKernelGGL((k_lattice<T, DEN, R>), grid((f + b.lp.per - 1) / b.lp.per), block, lds, st, cnt, W, den,
                                n, rr, f, v0, b.lp, flags);
             return;
         }
         const size_t row_lds = (size_t)b.row_lines * b.row_pitch * 4, col_lds = (size_t)b.col_lines * b.line.slots * 4;
-        allow_lds(k_rows3<R>, row_lds);
         hipLaunchKernelGGL(k_rows3<R>, grid((f * E + b.row_lines - 1) / b.row_lines), block, row_lds, st, cnt, rows, n,
                            rr, f * E, b.row_lines, b.row_pitch, b.line);
         if constexpr (R > 0) {
             hipLaunchKernelGGL((k_cols3_small<T, DEN, R>), grid((f * E + kBlurThreads - 1) / kBlurThreads), block, 0, st,
                                rows, W, den, n, f, v0, flags);
         } else {
-            allow_lds(k_cols3<T, DEN>, col_lds);
             hipLaunchKernelGGL((k_cols3<T, DEN>), grid(f * ((E + b.col_lines - 1) / b.col_lines)), block, col_lds, st,
                                rows, W, den, n, rr, f, v0, b.col_lines, b.line, flags);
         }
-    };
-    static_assert(kRegRadius == 8, "the radii below");
-    switch (b.small ? (int)r : 0) {
-    case 1: run(StaticInt<1>{}); break;
-    case 2: run(StaticInt<2>{}); break;
-    case 3: run(StaticInt<3>{}); break;
-    case 4: run(StaticInt<4>{}); break;
-    case 5: run(StaticInt<5>{}); break;
-    case 6: run(StaticInt<6>{}); break;
-    case 7: run(StaticInt<7>{}); break;
-    case 8: run(StaticInt<8>{}); break;
-    default: run(StaticInt<0>{}); break;
-    }
+    });
 }
 
 }  // namespace
@@ -1076,8 +1092,15 @@ hipError_t launch_update(bool f16, void *W, int64_t V, int64_t E, const int32_t 
                          const UpdateBuffers &ub, hipStream_t st)
 {
     const int64_t M = E * E;
+    const BlurPlan bp = blur_plan(E, radius);
+    hipError_t e = hipSuccess;
+    if (bp.feature_major()) {  // before anything is enqueued: an update that cannot run leaves the codebook as it is
+        e = allow_blur_lds<float, true>(bp, radius);
+        if (e == hipSuccess) e = f16 ? allow_blur_lds<_Float16, false>(bp, radius) : allow_blur_lds<float, false>(bp, radius);
+        if (e != hipSuccess) return e;
+    }
     // row pointers checked before any row is read: a batch that fails updates nothing
-    hipError_t e = launch_check_rows(row_ptr, N, nnz, ub.flags, st);
+    e = launch_check_rows(row_ptr, N, nnz, ub.flags, st);
     if (e != hipSuccess) return e;
     // den: counts, blur, kept in ub.den_blur; the samples of heavy units sorted by unit
     const unsigned sg = (unsigned)((N + 255) / 256 < kScanBlocks ? (N + 255) / 256 + 1 : kScanBlocks);
@@ -1091,7 +1114,6 @@ hipError_t launch_update(bool f16, void *W, int64_t V, int64_t E, const int32_t 
                        ub.hunit);
     hipLaunchKernelGGL(k_heavy_scatter, dim3(lg), dim3(1024), 0, st, bmu, N, M, ub.start, ub.slot, ub.hunit, ub.cursor,
                        ub.order);
-    const BlurPlan bp = blur_plan(E, radius);
     if (bp.feature_major())
         blur_lds<float, true>(bp, ub.den_cnt, ub.den_a, ub.den_blur, nullptr, 1, E, radius, 0, ub.flags, st);
     else
