@@ -46,6 +46,46 @@ inline bool rows_direct(int64_t N, int64_t M, int ta)
            (ta == 8 && ((N <= 1024 && pairs <= (int64_t)1 << 23) || (N <= 4096 && pairs <= (int64_t)3 << 20)));
 }
 
+// Consecutive tiles per sweep workgroup. Longer groups let a wave keep its strip's
+// norms over several tiles and keep the tiles in flight a compact stretch of the
+// (regrouped) batch, but a strip must still span enough rounds of resident workgroups, or
+// the chip works on two strips at once and their rows compete for L2.
+// fp32: 8 tiles from 12,000 on, then one in 16,384, up to 32 (V = 20,000, ms by group size:
+// 64 x 64, 31,250 tiles 1.48 at 4, 1.43 at 8 and 12, 1.50 at 32; 128 x 128, 15,000 tiles 2.86,
+// 2.82, 2.87, 3.36; 256 x 256, 7,500 tiles 6.12, 6.22, 6.54, 8.52; 1024 x 1024, 62,500 tiles
+// 784, 769, 812, 835; whole searches, V = 30,000, 64 x 64: 125,000 tiles 6.39 at 4, 6.32 at 8,
+// 6.34 at 12, 6.39 at 24; 250,000 tiles 12.60, 12.44, 12.45, 12.48).
+// fp16 rows are half as long, so two strips at once still fit and the tile's prologue and
+// neighbourhood count for more: 8 tiles from 1,500 on, 12 from 6,000, 16 from 12,000, 24 from
+// 20,000, 32 from 30,000 (256 x 256: 2,000 tiles 1.24 at 4, 1.20 at 8, 1.50 at 32; 7,500 tiles
+// 4.23, 4.01, 3.92; 25,000 tiles 13.46, 12.62, 11.99; 1024 x 1024, 62,500 tiles 552, 520, 491).
+// Tiles of 16 and 32 keep the line they were measured with.
+//
+// Those lines are for maps of many strips. All strips together must also give the chip
+// enough workgroups: it holds 1,024 of them, and a last round that is half empty costs more
+// than longer groups bring. So groups of tiles of 8 are shortened until there are kGroupRounds
+// rounds (whole searches, us, by the lines above alone / bounded so: fp16 16 x 16, 12,000 rows
+// 47 / 36, 100,000 rows 111 / 103; fp16 32 x 32, 50,000 rows 121 / 100; fp16 64 x 64, 250,000
+// rows 1,183 / 1,161; fp32 32 x 32, 100,000 rows 260 / 244; elsewhere the same within 1%).
+constexpr int64_t kResidentGroups = 1024;
+constexpr int64_t kGroupRounds = 13, kGroupRoundsF16 = 8;
+
+inline int64_t sweep_group_tiles(int64_t nt, int64_t strips, int ta, bool f16)
+{
+    int64_t g = nt / 16384 / 4 * 4;
+    if (ta != 8) {
+        if (g < 8 && nt >= 8 * 7500) g = 8;
+        return g < 4 ? 4 : (g > 32 ? 32 : g);
+    }
+    if (f16)
+        g = nt >= 30000 ? 32 : nt >= 20000 ? 24 : nt >= 12000 ? 16 : nt >= 6000 ? 12 : nt >= 1500 ? 8 : 4;
+    else if (g < 8 && nt >= 12000)
+        g = 8;
+    const int64_t most = nt * strips / ((f16 ? kGroupRoundsF16 : kGroupRounds) * kResidentGroups) / 4 * 4;
+    g = g < most ? g : most;
+    return g < 4 ? 4 : (g > 32 ? 32 : g);
+}
+
 // One position's result of a regrouped batch, staged in the workspace: a whole 16-byte
 // record, so the finalize writes full lines and the move back to input order reads one
 // record per sample.

@@ -556,37 +556,13 @@ static void sweep_ta(dim3 grid, int64_t group_tiles, hipStream_t st, const E *W,
     }
 }
 
-// Consecutive tiles per sweep workgroup. Longer groups let a wave keep its strip's
-// norms over several tiles and keep the tiles in flight a compact stretch of the
-// (regrouped) batch, but a strip must still span enough rounds of resident workgroups, or
-// the chip works on two strips at once and their rows compete for L2.
-// fp32: 8 tiles from 12,000 on, then one in 10,240, up to 32 (V = 20,000, ms by group size: 64 x 64, 31,250 tiles 1.48 at 4, 1.43 at 8 and 12, 1.50 at 32;
-// 128 x 128, 15,000 tiles 2.86, 2.82, 2.87, 3.36; 256 x 256, 7,500 tiles 6.12, 6.22, 6.54,
-// 8.52; 1024 x 1024, 62,500 tiles 784, 769, 812, 835).
-// fp16 rows are half as long, so two strips at once still fit and the tile's prologue and
-// neighbourhood count for more: 8 tiles from 1,500 on, 12 from 6,000, 16 from 12,000, 24 from
-// 20,000, 32 from 30,000 (256 x 256: 2,000 tiles 1.24 at 4, 1.20 at 8, 1.50 at 32; 7,500 tiles
-// 4.23, 4.01, 3.92; 25,000 tiles 13.46, 12.62, 11.99; 1024 x 1024, 62,500 tiles 552, 520, 491).
-// Tiles of 16 and 32 keep the line they were measured with.
-static int64_t sweep_group_tiles(int64_t nt, int ta, bool f16)
-{
-    if (ta != 8) {
-        int64_t g = nt / 16384 / 4 * 4;
-        if (g < 8 && nt >= 8 * 7500) g = 8;
-        return g < 4 ? 4 : (g > 32 ? 32 : g);
-    }
-    if (f16) return nt >= 30000 ? 32 : nt >= 20000 ? 24 : nt >= 12000 ? 16 : nt >= 6000 ? 12 : nt >= 1500 ? 8 : 4;
-    const int64_t g = nt / 10240 / 4 * 4, least = nt >= 12000 ? 8 : 4;
-    return g < least ? least : (g > 32 ? 32 : g);
-}
-
 template <typename E, bool TOP2>
 static hipError_t sweep_any(int ta, const E *W, const double *norms, int64_t M, int64_t N, int64_t V, int64_t nnz,
                             const uint2 *plan, const int2 *tiles, const float *vals, const SweepOut &o,
                             hipStream_t st)
 {
     const int64_t nt = n_tiles(N, ta);
-    const int64_t gt = sweep_group_tiles(nt, ta, sizeof(E) == 2);
+    const int64_t gt = sweep_group_tiles(nt, n_strips(M, ta), ta, sizeof(E) == 2);
     int64_t gx = (nt + gt - 1) / gt;
     if (gx > (1 << 20)) gx = 1 << 20;
     const dim3 grid((unsigned)gx, (unsigned)n_strips(M, ta));

@@ -1,0 +1,10 @@
+// rules.cpp -- the host's rules on sizes (som_internal.h), for tests/test_rules.py.
+#include "../../paper_2608_24067_amd/csrc/som_internal.h"
+
+extern "C" {
+int64_t group_tiles(int64_t nt, int64_t strips, int32_t ta, int32_t f16)
+{
+    return som::sweep_group_tiles(nt, strips, ta, f16 != 0);
+}
+int64_t strips(int64_t M, int32_t ta) { return som::n_strips(M, ta); }
+}
