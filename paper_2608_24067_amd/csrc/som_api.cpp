@@ -259,7 +259,7 @@ som_status search_impl(const Book &b, const Kind &k, const double *norms, int64_
     if ((st = check_book(b, who)) != SOM_OK) return st;
     if ((st = setup(N, M, V, nnz, config, workspace, workspace_bytes, k, &o, &c, &noop)) != SOM_OK) return st;
     if (noop) return ok();
-    if (som::rows_direct(N, M, o.ta)) {
+    if (som::rows_direct(N, M, nnz, o.ta, b.f16)) {
         const som::DirectRows d{row_ptr, col_idx, values, o.ta, c.plan, c.tiles, c.vals, c.xsq, c.flags};
         som::SweepOut out = c.out;
         out.direct = &d;

@@ -32,18 +32,46 @@ inline int64_t n_tiles(int64_t N, int ta) { return (N + ta - 1) / ta; }
 // within 4%; the plan does not know the codebook's type.
 inline bool regroup_pays(int64_t N, int64_t M) { return M > 512 && N >= 8192 && N * M >= (int64_t)1 << 28; }
 
-// Whether a search reads its rows without a plan (som_rows.hip). That saves two launches and
-// the walk over tiles' unions, and reads a codebook row once per sample instead of once per
-// tile: it wins while the rows times the units are few. Without / with the plan, us, fp32:
-// 64 x 64 map 13.8 / 27 at one row, 15 / 36 at 512, 23 / 37 at 1,024, 44 / 44 at 2,048;
-// 256 x 256 28 / 43 at 64, 88 / 101 at 256, 165 / 161 at 512; 512 x 512 61 / 86 at 33,
-// 114 / 114 at 64 (fp16: 62 / 67); 16 x 16 map 14 / 33 at 2,048, 22 / 33 at 4,096; 32 x 32 19 /
-// 36 at 2,048, 36 / 37 at 4,096.
-inline bool rows_direct(int64_t N, int64_t M, int ta)
+// Sizes at which a search may read its rows without a plan (som_rows.hip). That saves two
+// launches and the walk over tiles' unions, and reads a codebook row once per sample instead
+// of once per tile: it wins while the rows times the units are few. Without / with the plan,
+// us, fp32, 12 ids a row: 64 x 64 map 13.8 / 27 at one row, 15 / 36 at 512, 23 / 37 at 1,024,
+// 44 / 44 at 2,048; 256 x 256 28 / 43 at 64, 88 / 101 at 256, 165 / 161 at 512; 512 x 512
+// 61 / 86 at 33, 114 / 114 at 64 (fp16: 62 / 67); 16 x 16 map 14 / 33 at 2,048, 22 / 33 at
+// 4,096; 32 x 32 19 / 36 at 2,048, 36 / 37 at 4,096.
+inline bool few_rows(int64_t N, int64_t M, int ta)
 {
     const int64_t pairs = N * M;
     return (N <= 256 && pairs <= (int64_t)1 << 24) ||
            (ta == 8 && ((N <= 1024 && pairs <= (int64_t)1 << 23) || (N <= 4096 && pairs <= (int64_t)3 << 20)));
+}
+
+// Whether it does at nnz ids in all. Longer rows keep to the line above while a launch is
+// short of waves, since a plan's walk grows with the row too. Once it is not, the codebook
+// rows that samples share are read by each of them, and the ids times the units are the work.
+// Without / with the plan, us, by the rows and the ids of each (tests on Zipf rows, V = 30,000):
+// - up to 2^15 units, fp32: 64 x 64, 1,024 rows of 1,000 889 / 3,100; 128 x 128, 512 of 4,000 9,384 /
+//   12,670; 32 x 32, 3,000 of 15,000 10,743 / 21,973;
+// - up to 2^17: 256 x 256, 64 of 4,000 7,344 / 7,868; 96 of 1,000 2,858 / 3,590; 256 of 200 1,473 /
+//   1,487, of 400 3,020 / 2,750; fp16 64 of 4,000 3,518 / 6,821, 192 of 1,000 2,736 / 3,451;
+// - above: 512 x 512, 16 of 1,000 2,464 / 2,886, of 4,000 9,863 / 8,582; 32 of 400 1,949 / 1,703; 64 of
+//   100 908 / 797, of 1,000 9,863 / 6,198; fp16 64 of 200 925 / 972, of 400 1,847 / 1,722.
+// Below 5 * 2^20 pairs the plan's launch has a quarter of the chip's waves. A single row
+// shares nothing.
+inline bool rows_direct(int64_t N, int64_t M, int64_t nnz, int ta, bool f16)
+{
+    if (!few_rows(N, M, ta)) return false;
+    const bool thin = N * M <= (int64_t)5 << 20;
+    int64_t most, times16 = 4;  // ids times units; so many times that with fp16 rows
+    if (M <= 1 << 15) {
+        most = (int64_t)1 << 36;
+    } else if (M <= 1 << 17) {
+        most = (int64_t)(thin ? 16 : 6) << 30;
+        times16 = 2;
+    } else {
+        most = (int64_t)(thin ? 12 : 3) << 29;
+    }
+    return N == 1 || nnz * M <= (f16 ? times16 : 1) * most;
 }
 
 // Consecutive tiles per sweep workgroup. Longer groups let a wave keep its strip's

@@ -21,6 +21,7 @@ def rules(tmp_path_factory):
     lib = ctypes.CDLL(out)
     i64, i32 = ctypes.c_int64, ctypes.c_int32
     lib.group_tiles.argtypes, lib.group_tiles.restype = [i64, i64, i32, i32], i64
+    lib.rows_direct.argtypes = [i64, i64, i64, i32, i32]
     lib.strips.argtypes, lib.strips.restype = [i64, i32], i64
     return lib
 
@@ -41,3 +42,23 @@ def test_long_tile_groups_leave_enough_workgroups(rules, f16):
 def test_tile_groups_of_many_strips_are_long(rules):
     assert rules.group_tiles(62500, 2048, 8, 0) == 8 and rules.group_tiles(62500, 2048, 8, 1) == 32
     assert rules.group_tiles(2000, 2048, 8, 1) == 8 and rules.group_tiles(31250, 8, 8, 0) == 8
+
+
+@pytest.mark.parametrize("f16", [0, 1])
+def test_searches_without_a_plan_end_where_long_rows_are_shared(rules, f16):
+    """Few rows of a dozen ids are searched without a plan; rows of hundreds of ids on a large map, whose codebook
+    rows a plan reads once per tile instead of once per sample, are not (at 1,000 ids each: 64 rows on 512 x 512)."""
+    def direct(N, M, ids, ta=8):
+        return rules.rows_direct(N, M, N * ids, ta, f16)
+
+    for N, M in ((1, 4096), (33, 65536), (64, 1 << 18), (16, 1 << 20), (256, 65536), (1024, 4096), (4096, 256)):
+        assert direct(N, M, 12), (N, M)
+    for N, M in ((64, 1 << 18), (48, 1 << 18), (16, 1 << 20), (256, 65536)):
+        assert not direct(N, M, 1000), (N, M)
+    for N, M in ((8, 1 << 18), (64, 65536), (512, 16384), (1024, 4096), (4096, 256), (1, 1 << 20)):
+        assert direct(N, M, 1000), (N, M)
+    for N, M in ((2, 1 << 20), (20, 1 << 18), (64, 1 << 18), (200, 65536), (100, 65536), (1024, 8192), (4096, 700)):
+        took = [direct(N, M, ids) for ids in (0, 1, 12, 100, 300, 1000, 3000, 10000, 10**5, 10**6)]
+        assert took == sorted(took, reverse=True), (N, M)  # longer rows never return to it
+        assert not took[-1]
+    assert not direct(257, 4096, 12, ta=16) and not direct(4097, 256, 12) and not direct(1025, 1 << 13, 12)
