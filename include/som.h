@@ -97,7 +97,7 @@ typedef enum {
  *   tile_samples  samples per tile, TA (SpMM-tile kernel section): 8, 16 or
  *                 32; 0 selects SOM_DEFAULT_TILE_SAMPLES.
  *   keep_order    0 (default): where it pays (large batches on maps of more
- *                 than 512 units), the plan first regroups the batch by each
+ *                 than 256 units), the plan first regroups the batch by each
  *                 sample's least frequent feature (the post-submission
  *                 section's lever of clustering samples so tiles share
  *                 features), which shrinks tile unions and keeps rare

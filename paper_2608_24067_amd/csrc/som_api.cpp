@@ -190,7 +190,7 @@ som_status plan_impl(const int32_t *row_ptr, const int32_t *col_idx, const float
     hipStream_t s = static_cast<hipStream_t>(stream);
     hipError_t e = som::launch_check_rows(row_ptr, N, nnz, c.flags, s);
     if (e != hipSuccess) return hip_fail(e, who);
-    const bool order = o.order && som::regroup_pays(N, M);
+    const bool order = o.order && som::regroup_pays(N, M, nnz, o.ta);
     if (order) {
         e = som::launch_order(row_ptr, col_idx, N, nnz, V, c.ob, c.flags, s);
         if (e != hipSuccess) return hip_fail(e, who);
@@ -235,7 +235,7 @@ som_status finalize_impl(const Kind &k, const double *norms, int64_t V, int64_t 
         return fail(SOM_ERR_INVALID_ARG, "%s: null pointer", who);
     if ((st = setup(N, M, V, nnz, config, workspace, workspace_bytes, k, &o, &c, &noop)) != SOM_OK) return st;
     if (noop) return ok();
-    const bool order = o.order && som::regroup_pays(N, M);  // as the plan decided
+    const bool order = o.order && som::regroup_pays(N, M, nnz, o.ta);  // as the plan decided
     hipError_t e = som::launch_finalize(o.ta, norms, M, row_ptr, N, nnz, order ? &c.ob : nullptr, c.xsq, c.out, bmu,
                                         dist, k.top2 ? bmu2 : nullptr, k.top2 ? dist2 : nullptr,
                                         static_cast<hipStream_t>(stream));

@@ -21,17 +21,6 @@ inline int64_t strip_neurons(int ta) { return 64 * neurons_per_lane(ta); }
 inline int64_t n_strips(int64_t M, int ta) { return (M + strip_neurons(ta) - 1) / strip_neurons(ta); }
 inline int64_t n_tiles(int64_t N, int ta) { return (N + ta - 1) / ta; }
 
-// Whether regrouping a batch by rarest features pays (its caller allowing it). Six kernels
-// and the scattered reads they cause cost 35-45 us and 0.2 ns a row; the sweep then reads
-// rare rows from L2 more often, 1% faster at 16,000 rows and 18-21% at 2,000,000 (fp32;
-// 4-6% for fp16), where the strips do not fit there anyway. Whole searches, fp32, V = 30,000,
-// regrouped / as given: 64 x 64 map 316 / 289 us at 32,000 rows, 521 / 521 at 64,000, 909 /
-// 976 at 128,000; 256 x 256 777 / 738 at 4,000, 1,272 / 1,255 at 8,000, 2,200 / 2,236 at
-// 16,000; 32 x 32 511 / 511 at 256,000; a map of one strip never gains (16 x 16: 1,620 /
-// 1,466 at 2,000,000). fp16 sweeps gain less and break even at two to four times the rows,
-// within 4%; the plan does not know the codebook's type.
-inline bool regroup_pays(int64_t N, int64_t M) { return M > 512 && N >= 8192 && N * M >= (int64_t)1 << 28; }
-
 // Sizes at which a search may read its rows without a plan (som_rows.hip). That saves two
 // launches and the walk over tiles' unions, and reads a codebook row once per sample instead
 // of once per tile: it wins while the rows times the units are few. Without / with the plan,
@@ -72,6 +61,29 @@ inline bool rows_direct(int64_t N, int64_t M, int64_t nnz, int ta, bool f16)
         most = (int64_t)(thin ? 12 : 3) << 29;
     }
     return N == 1 || nnz * M <= (f16 ? times16 : 1) * most;
+}
+
+// Whether regrouping a batch by rarest features pays (its caller allowing it). Six kernels
+// and the scattered reads they cause cost 35-45 us and 0.2 ns a row; the sweep then reads
+// rare rows from L2 more often, 1% faster at 16,000 rows and 18-21% at 2,000,000 (fp32;
+// 4-6% for fp16), where the strips do not fit there anyway, and far more where rows
+// resemble each other. A batch's likeness is not known beforehand, so the line lies where
+// independent rows lose at most a tenth and like ones do not yet gain more: from 9 * 2^28
+// ids times units on, at 12 ids a row 49,000 rows on a 64 x 64 map. Whole searches, us, fp32,
+// V = 30,000, regrouped / as given, for independent rows; for eight variants of each row (a tenth
+// of the ids changed); for eight copies: 64 x 64 map 335 / 305, 216 / 277, 166 / 273 at 32,000 rows,
+// 555 / 556, 376 / 530, 281 / 522 at 64,000; 128 x 128 635 / 606, 412 / 534, 288 / 509 at 16,000;
+// 256 x 256 491 / 446, 326 / 369, 183 / 339 at 2,000, 801 / 758, 490 / 600, 297 / 561 at 4,000;
+// 22 x 22 592 / 578, 462 / 576, 400 / 578 at 512,000. Longer rows gain as the product says (fp16
+// 64 x 64, 30,000 rows of 200 ids 1,984 / 2,502). Maps of up to 256 units, half a strip, read too
+// little per row (16 x 16, 2,000,000 rows 1,673 / 1,558, 1,534 / 1,555, 1,432 / 1,561).
+// fp16 sweeps gain less (64 x 64, 64,000 rows 365 / 337, 320 / 334, 276 / 334); the plan and the
+// finalize do not know the codebook's type. Nor do they know of a search that ran without a
+// plan: its workspace holds the rows in the order given, so wherever one may (an fp16 one, the
+// wider line) the phases regroup nothing.
+inline bool regroup_pays(int64_t N, int64_t M, int64_t nnz, int ta)
+{
+    return M > 256 && nnz * M >= (int64_t)9 << 28 && !rows_direct(N, M, nnz, ta, true);
 }
 
 // Consecutive tiles per sweep workgroup. Longer groups let a wave keep its strip's

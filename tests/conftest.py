@@ -1,4 +1,6 @@
+import ctypes
 import os
+import subprocess
 import sys
 
 import pytest
@@ -19,6 +21,21 @@ def gpu_available() -> bool:
         return torch.cuda.is_available()
     except Exception:
         return False
+
+
+@pytest.fixture(scope="session")
+def rules(tmp_path_factory):
+    """The rules that choose a path or a launch by sizes, built for the host (tests/host/rules.cpp)."""
+    out = str(tmp_path_factory.mktemp("rules") / "librules.so")
+    subprocess.run(["g++", "-std=c++17", "-Wall", "-O1", "-fPIC", "-shared", "-D__HIP_PLATFORM_AMD__",
+                    "-I/opt/rocm/include", "-Iinclude", "tests/host/rules.cpp", "-o", out], cwd=ROOT, check=True)
+    lib = ctypes.CDLL(out)
+    i64, i32 = ctypes.c_int64, ctypes.c_int32
+    lib.group_tiles.argtypes, lib.group_tiles.restype = [i64, i64, i32, i32], i64
+    lib.rows_direct.argtypes = [i64, i64, i64, i32, i32]
+    lib.regroups.argtypes = [i64, i64, i64, i32]
+    lib.strips.argtypes, lib.strips.restype = [i64, i32], i64
+    return lib
 
 
 @pytest.fixture(scope="session")

@@ -63,10 +63,11 @@ def test_ragged_shapes(dev, seed, N, V, M, kind, tile, keep):
     compare(W, rp, ci, b, d, exact=(kind == synth.QUANTISED), what=f"N={N} V={V} M={M} TA={tile} keep={keep}")
 
 
-def test_tile_size_order_and_repeat_invariance(dev):
+def test_tile_size_order_and_repeat_invariance(dev, rules):
     # each sample's dot is its own ascending fp32 sum, so neither the tile size nor the
     # regrouping of samples can change a bit
-    rp, ci, W = case(31, 3000, 30000, 2500, synth.UNIFORM)
+    rp, ci, W = case(31, 15000, 3000, 16500, synth.UNIFORM)
+    assert all(rules.regroups(15000, 16500, len(ci), t) for t in (8, 16, 32))
     runs = [gpu_run(W, rp, ci, dev, tile_samples=t, keep_order=k)[:2]
             for t, k in ((8, False), (16, False), (32, False), (8, True), (16, True), (32, True), (8, False))]
     for b, d in runs[1:]:

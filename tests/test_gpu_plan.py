@@ -84,13 +84,14 @@ def test_invalid_ids_in_a_short_tile_are_flagged_and_stay_local(dev, how):
 
 
 @pytest.mark.parametrize("vocabulary", [3, 8193, 32769, 70001])
-def test_regrouped_batch_equals_the_given_order(dev, vocabulary):
-    # 263,000 rows on 1,024 units are regrouped: feature counts in LDS (both sizes) and in
+def test_regrouped_batch_equals_the_given_order(dev, rules, vocabulary):
+    # 263,000 rows on 2,000 units (6,000 where rows hold two ids) are regrouped: feature counts in LDS (both sizes) and in
     # global memory, the bucket scan in one and in several steps, its last words ragged
     import torch
 
-    N, units = 263_000, 1024
+    N, units = 263_000, 6000 if vocabulary == 3 else 2000
     rp, ci = synth.make_csr(31, N, vocabulary, lam=2.0 if vocabulary == 3 else 6.0)
+    assert rules.regroups(N, units, len(ci), 8)
     g = torch.Generator(device=dev).manual_seed(5)
     W = torch.rand((vocabulary, units), device=dev, generator=g)
     given = gpu_run2(W, rp, ci, dev, keep_order=True)

@@ -61,8 +61,9 @@ def test_rank1_equals_single_best_search(dev):
         assert np.array_equal(g[0], b) and np.array_equal(g[1], d), f"seed {seed}"
 
 
-def test_tile_and_order_invariance(dev):
-    rp, ci, W = case(49, 900, 2500, 1300, synth.UNIFORM)
+def test_tile_and_order_invariance(dev, rules):
+    rp, ci, W = case(49, 15000, 800, 16500, synth.UNIFORM)
+    assert all(rules.regroups(15000, 16500, len(ci), t) for t in (8, 16, 32))
     runs = [gpu_run2(W, rp, ci, dev, tile_samples=t, keep_order=k) for t in (8, 16, 32) for k in (False, True)]
     for r in runs[1:]:
         for a, b in zip(runs[0], r):

@@ -1,29 +1,7 @@
 """The rules that choose a path or a launch by sizes, built for the host (tests/host/rules.cpp)."""
-import ctypes
-import os
-import shutil
-import subprocess
-
 import pytest
 
-ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 RESIDENT = 1024  # sweep workgroups the chip holds: 256 compute units, four each
-
-pytestmark = pytest.mark.skipif(shutil.which("g++") is None or not os.path.isdir("/opt/rocm/include"),
-                                reason="needs g++ and the ROCm headers")
-
-
-@pytest.fixture(scope="module")
-def rules(tmp_path_factory):
-    out = str(tmp_path_factory.mktemp("rules") / "librules.so")
-    subprocess.run(["g++", "-std=c++17", "-Wall", "-O1", "-fPIC", "-shared", "-D__HIP_PLATFORM_AMD__",
-                    "-I/opt/rocm/include", "-Iinclude", "tests/host/rules.cpp", "-o", out], cwd=ROOT, check=True)
-    lib = ctypes.CDLL(out)
-    i64, i32 = ctypes.c_int64, ctypes.c_int32
-    lib.group_tiles.argtypes, lib.group_tiles.restype = [i64, i64, i32, i32], i64
-    lib.rows_direct.argtypes = [i64, i64, i64, i32, i32]
-    lib.strips.argtypes, lib.strips.restype = [i64, i32], i64
-    return lib
 
 
 @pytest.mark.parametrize("f16", [0, 1])
@@ -62,3 +40,24 @@ def test_searches_without_a_plan_end_where_long_rows_are_shared(rules, f16):
         assert took == sorted(took, reverse=True), (N, M)  # longer rows never return to it
         assert not took[-1]
     assert not direct(257, 4096, 12, ta=16) and not direct(4097, 256, 12) and not direct(1025, 1 << 13, 12)
+
+
+def test_regrouping_covers_batches_whose_rows_may_resemble_each_other(rules):
+    """Regrouping is left out only where its kernels cost a tenth of the sweep or more, whatever the number of rows."""
+    for N, M, ids in ((64000, 4096, 12), (16000, 16384, 12), (4000, 65536, 12), (8000, 65536, 12), (512000, 484, 12),
+                      (30000, 4096, 200), (500000, 1 << 20, 12), (200, 1 << 20, 12)):
+        assert rules.regroups(N, M, N * ids, 8), (N, M, ids)
+    for N, M, ids in ((32000, 4096, 12), (2000, 65536, 12), (2000000, 256, 12), (128000, 484, 12), (10000, 256, 12)):
+        assert not rules.regroups(N, M, N * ids, 8), (N, M, ids)
+
+
+def test_no_search_without_a_plan_where_phases_regroup(rules):
+    """A workspace that a search without a plan leaves holds the rows in the order given, as the phases must read it."""
+    for ta in (8, 16, 32):
+        for M in (1, 256, 257, 700, 4096, 32768, 32769, 65536, 131073, 1 << 18, 1 << 20):
+            for N in (1, 2, 8, 48, 64, 256, 257, 1024, 1025, 4096, 4097, 10**6):
+                for ids in (0, 1, 12, 100, 400, 1000, 4000, 15000, 30000):
+                    if N * ids >= 2**31:
+                        continue
+                    if rules.regroups(N, M, N * ids, ta):
+                        assert not any(rules.rows_direct(N, M, N * ids, ta, f16) for f16 in (0, 1)), (N, M, ids, ta)
