@@ -45,7 +45,7 @@ def test_tiny_workload_bit_exact(dev):
 
 
 SHAPES = [
-    # M off multiples of 8 takes the scalar load path
+    # M off multiples of 8 reads its rows at any element's address, below 8 element by element
     (61, 1, 50, 1, synth.QUANTISED),
     (62, 17, 300, 5, synth.QUANTISED),
     (63, 1000, 2000, 300, synth.QUANTISED),

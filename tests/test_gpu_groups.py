@@ -1,9 +1,9 @@
 """GPU parity when the sweep's workgroups take long groups of consecutive tiles.
 
 A batch of 1.1 M rows gives 137,500 tiles of 8, enough for groups of 8 tiles per
-workgroup (two per wave) -- the smaller parity tests run with groups of 4, and the
-full-size workloads check samples only. A k/256 codebook with 1,100 neurons (two
-strips, the second ragged) and k/256 values make every distance exact, so each
+workgroup (two per wave; 32 for an fp16 codebook) -- the smaller parity tests run with
+groups of 4, and the full-size workloads check samples only. A k/256 codebook with 1,100
+neurons (three strips, the last ragged) and k/256 values make every distance exact, so each
 form of the search is compared bit for bit with the oracle on 1,500 rows spread
 over the whole batch, and the forms are compared with each other on every row:
 fp16 storage of a k/256 codebook is exact, and unit values reproduce the binary
@@ -24,7 +24,8 @@ N, V, M, SEED = 1_100_000, 2000, 1100, 121
 
 
 @pytest.fixture(scope="module")
-def batch():
+def batch(rules):
+    assert [rules.group_tiles(-(-N // 8), rules.strips(M, 8), 8, f16) for f16 in (0, 1)] == [8, 32]
     rp, ci = synth.make_csr(SEED, N, V)
     W = synth.codebook(SEED, synth.QUANTISED, V, M)
     vals = synth.values(SEED, len(ci), synth.VAL_QUANTISED)

@@ -34,6 +34,20 @@ def test_norms_match_oracle_bitwise(dev, V, M, kind):
     assert np.array_equal(n_gpu, n_ref)
 
 
+# Maps of up to 16,384 units bring their rows in chunks of 112, three in flight; up to 32,704 a
+# lane reads 128 rows at a time, beyond that 32. Units and rows on both sides of each line.
+NORM_SHAPES = [(v, 130) for v in (1, 2, 111, 112, 113, 224, 335, 336, 337, 448, 449, 673)] + \
+              [(v, m) for v in (1, 31, 32, 33, 127, 128, 129, 300) for m in (16384, 16385, 32704, 32705, 40001)]
+
+
+@pytest.mark.parametrize("dtype", [np.float32, np.float16])
+@pytest.mark.parametrize("V,M", NORM_SHAPES)
+def test_norms_of_every_form_match_oracle_bitwise(dev, V, M, dtype):
+    W = synth.codebook(V + M, synth.UNIFORM, V, M).astype(dtype)
+    n = som.codebook_norms(to_dev(W, dev), V, M).cpu().numpy()
+    assert np.array_equal(n, oracle.norms(W.astype(np.float32)))
+
+
 def test_tiny_workload_bit_exact(dev):
     # the whole 16x16 workload (10,000 rows, V=2000, k/256): every index and distance exact
     cfg = synth.CONFIGS["tiny"]
@@ -134,20 +148,27 @@ def long_rows(seed, N, V, lo, hi):
 
 @pytest.mark.parametrize("tile,keep", [(8, False), (16, False), (32, True)])
 def test_long_rows_plan_from_global_memory(dev, tile, keep):
+    from test_gpu_row_loads import phases
+
     rp, ci = long_rows(141, 300, 600, 30, 70)
     W = synth.codebook(141, synth.QUANTISED, 600, 700)
     b, d, _ = gpu_run(W, rp, ci, dev, tile_samples=tile, keep_order=keep)
     compare(W, rp, ci, b, d, exact=True, what=f"long rows tile {tile}")
+    # tiles of 8: so few rows are searched without a plan, unless in phases
+    compare(W, rp, ci, *phases(to_dev(W, dev), rp, ci, dev, tile, False), exact=True, what=f"planned, tile {tile}")
 
 
 def test_long_rows_real_values(dev):
     from parity import compare_sf, gpu_run_sf
+    from test_gpu_row_loads import phases
 
     rp, ci = long_rows(142, 200, 500, 30, 70)
     W = synth.codebook(142, synth.QUANTISED, 500, 300)
     vals = synth.values(142, len(ci), synth.VAL_QUANTISED)
     g = gpu_run_sf(W, rp, ci, vals, dev)
     compare_sf(W, rp, ci, vals, g, exact=True, what="long rows, real values")
+    planned = phases(to_dev(W, dev), rp, ci, dev, 8, True, vals)
+    compare_sf(W, rp, ci, vals, planned, exact=True, what="long rows, real values, planned")
 
 
 @pytest.mark.parametrize("two_best", [False, True])
@@ -282,8 +303,8 @@ def test_negative_first_offset_reads_as_empty(dev, tile, keep):
 def test_decreasing_row_ptr_reads_as_empty(dev, tile, keep):
     """Row pointers that decrease would let rows overlap ([0, nnz, 0, nnz, ...]: every even row spans the whole
     batch) and multiply the work. They are checked before any row is read: the batch is flagged and searched as if
-    every row were empty, so every sample gets the unit of smallest norm, lowest index first (its distance too, when
-    the batch is regrouped: the regrouped rows are all empty). The sizes keep even the overlapping walk short."""
+    every row were empty, so every sample gets the unit of smallest norm, lowest index first, and that norm as its
+    distance. The sizes keep even the overlapping walk short."""
     V, M, N = 300, 500, 2000
     rp, ci, W = case(44, N, V, M, synth.UNIFORM)
     nnz = int(rp[-1])
@@ -306,10 +327,9 @@ def test_decreasing_row_ptr_reads_as_empty(dev, tile, keep):
         assert (res[0] == order[0]).all()
         if two:
             assert (res[2] == order[1]).all()
-        if not keep:
-            assert (res[1] == nrm[order[0]]).all()
-            if two:
-                assert (res[3] == nrm[order[1]]).all()
+        assert (res[1] == nrm[order[0]]).all()
+        if two:
+            assert (res[3] == nrm[order[1]]).all()
 
 
 @pytest.mark.parametrize("name,rows", [("64", 4096), ("256", 1024), ("512", 256)])
