@@ -517,7 +517,6 @@ static som_status update_impl(const Book &b, void *W, int64_t V, int64_t E, cons
     ub.flags = reinterpret_cast<uint32_t *>(w + L.flags);
     ub.den_cnt = reinterpret_cast<int32_t *>(w + L.den_cnt);
     ub.sup_row = reinterpret_cast<int32_t *>(w + L.sup_row);
-    ub.sup = reinterpret_cast<int32_t *>(w + L.sup);
     ub.den_a = reinterpret_cast<float *>(w + L.den_a);
     ub.den_b = reinterpret_cast<float *>(w + L.den_b);
     ub.den_blur = reinterpret_cast<float *>(w + L.den_blur);

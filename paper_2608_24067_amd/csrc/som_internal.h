@@ -261,14 +261,16 @@ hipError_t launch_order(const int32_t *row_ptr, const int32_t *col_idx, int64_t 
 
 // ----------------------------------------------------------------- update
 
-// Workspace of the batch update (som_update.hip): the den field (counts and two
-// float buffers, M each), the sort of heavy units' samples (start[M + 2],
-// cursor[M], slot[M], hunit[M], order[N]) and, for one chunk of features, counts
-// and two float buffers of chunk * M.
+// Workspace of the batch update (som_update.hip): the den field (counts, occupied units
+// along the rows, and three float buffers, M each), the sort of heavy units' samples
+// (start[M + 2], cursor[M], slot[M], hunit[M], order[N]) and three fields of chunk * M
+// words, one after the other: the counts of a chunk of features and two float buffers where
+// the blur runs through memory (cnt, a, b), the counts of three chunks, from cnt on through a
+// and b, where it runs in LDS.
 struct UpdateBuffers {
     uint32_t *flags;  // SOM_FLAG_ROW_PTR: the batch's row pointers are invalid, nothing is updated
     int32_t *den_cnt;
-    int32_t *sup_row, *sup;  // occupied units in reach along the row (the column windows need no buffer: sup is free)
+    int32_t *sup_row;      // occupied units in reach along the row
     float *den_a, *den_b;  // scratch of the den blur
     float *den_blur;       // the blurred den
     int32_t *start, *cursor, *slot, *hunit, *order;
@@ -277,7 +279,7 @@ struct UpdateBuffers {
 };
 
 struct UpdateLayout {
-    size_t flags, den_cnt, sup_row, sup, den_a, den_b, den_blur, start, cursor, slot, hunit, order, cnt, a, b, total;
+    size_t flags, den_cnt, sup_row, den_a, den_b, den_blur, start, cursor, slot, hunit, order, cnt, a, b, total;
 };
 
 inline UpdateLayout update_layout(int64_t M, int64_t N, int64_t chunk)
@@ -292,7 +294,6 @@ inline UpdateLayout update_layout(int64_t M, int64_t N, int64_t chunk)
     L.flags = take(256);
     L.den_cnt = take((size_t)M * 4);
     L.sup_row = take((size_t)M * 4);
-    L.sup = take((size_t)M * 4);
     L.den_a = take((size_t)M * 4);
     L.den_b = take((size_t)M * 4);
     L.den_blur = take((size_t)M * 4);
@@ -301,9 +302,10 @@ inline UpdateLayout update_layout(int64_t M, int64_t N, int64_t chunk)
     L.slot = take((size_t)M * 4);
     L.hunit = take((size_t)M * 4);
     L.order = take((size_t)N * 4);
-    L.cnt = take((size_t)chunk * (size_t)M * 4);
-    L.a = take((size_t)chunk * (size_t)M * 4);
-    L.b = take((size_t)chunk * (size_t)M * 4);
+    const size_t field = align256((size_t)chunk * (size_t)M * 4);
+    L.cnt = take(3 * field);
+    L.a = L.cnt + field;
+    L.b = L.a + field;
     L.total = off;
     return L;
 }

@@ -588,10 +588,10 @@ __device__ __forceinline__ void line_pass3(const float *x, float *y, int n, int 
     p.run(n, [&](int t) { return x[t * step]; }, [&](int i, float v) { y[i * step] = v; });
 }
 
-// Offsets of a line's six (rows, then columns) or three passes; see above.
+// Offsets of a line's three passes (rows and columns alike); see above.
 struct LinePlan {
     int slots;    // per line
-    int off[4];   // where the input of pass 1, 2, 3 and the result start
+    int off[4];   // where the input of passes 1, 2 and 3 and the result start
 };
 
 inline LinePlan line_plan(int64_t n, int64_t r)
