@@ -1,4 +1,4 @@
-// rules.cpp -- the host's rules on sizes (som_internal.h), for the tests (fixture `rules`).
+// rules.cpp -- the host's rules on sizes (som_rules.h), for the tests (fixture `rules`).
 #include "../../paper_2608_24067_amd/csrc/som_internal.h"
 
 extern "C" {
