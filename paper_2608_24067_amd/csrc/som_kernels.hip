@@ -444,9 +444,9 @@ __device__ __forceinline__ int plan_merge(const IdAt &id_at, int p, int pe, int 
     // Every step consumes at least one id of the group, so a tile takes at most as many
     // steps as its span holds ids; only lanes whose ranges overlap (row pointers that
     // decrease, flagged above) take more, and their surplus entries are dropped.
-    while (true) {
-        const int m = group_min_i32<TA>(cur);
-        if (__ballot(m != INT_MAX) == 0) break;
+    // (Left by a break in its middle, the loop carries its exit condition to its end, four
+    // scalar instructions a step: 500,000 rows 57 -> 51 us.)
+    for (int m = group_min_i32<TA>(cur); __ballot(m != INT_MAX) != 0; m = group_min_i32<TA>(cur)) {
         const u64 bal = __ballot(m != INT_MAX && cur == m);
         const unsigned mask = (unsigned)((bal >> (grp * TA)) & (TA == 32 ? 0xFFFFFFFFull : ((1ull << TA) - 1)));
         if (m != INT_MAX) {
