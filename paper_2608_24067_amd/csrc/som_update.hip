@@ -609,19 +609,30 @@ __device__ __forceinline__ E quotient(float num, float den)
 }
 
 // The words of a lattice (rows of n) as a workgroup of T threads visits them, word t, t + T,
-// ...: LDS places follow by additions from the one before.
+// ...: LDS places follow by additions from the one before. MANY: of several lattices one after
+// the other, `words` places apart, with the unit each word belongs to.
+template <bool MANY>
 struct Walk {
     int c, at;          // column, place (row * pitch + column)
     int dc, dat, wrap;  // per step: columns and places on; a place more per row begun early
     int n;
-    __device__ Walk(int t, int T, int n_, int pitch) : n(n_)
+    int r, dr, gap;     // MANY: row, rows on per step, places left out between lattices
+    __device__ Walk(int t, int T, int n_, int pitch, int words) : n(n_)
     {
         c = t % n;
         at = t / n * pitch + c;
         dc = T % n;
         dat = T / n * pitch + dc;
         wrap = pitch - n;
+        if constexpr (MANY) {
+            gap = words - n * pitch;
+            r = t / n % n;
+            at += t / (n * n) * gap;
+            dr = T / n % n;
+            dat += T / (n * n) * gap;
+        }
     }
+    __device__ int unit() const { return r * n + c; }  // of the word next() is about to give
     __device__ int next()
     {
         const int place = at;
@@ -630,6 +641,12 @@ struct Walk {
         const bool over = c >= n;
         c -= over ? n : 0;
         at += over ? wrap : 0;
+        if constexpr (MANY) {
+            r += dr + (over ? 1 : 0);
+            const bool past = r >= n;  // once at most: dr < n
+            r -= past ? n : 0;
+            at += past ? gap : 0;
+        }
         return place;
     }
 };
@@ -637,10 +654,11 @@ struct Walk {
 // words words of src (integer counts) to LDS, LOADS per thread in flight; and back out of
 // LDS: quotients by den (units without a positive den keep what they have) or, for DEN,
 // the floats themselves.
-template <int LOADS>
-__device__ __forceinline__ void stage_in(const int32_t *src, float *lat, int words, int t, int T, int n, int pitch)
+template <int LOADS, bool MANY = false>
+__device__ __forceinline__ void stage_in(const int32_t *src, float *lat, int words, int t, int T, int n, int pitch,
+                                         int apart = 0)
 {
-    Walk w(t, T, n, pitch);
+    Walk<MANY> w(t, T, n, pitch, apart);
     for (int k0 = t; k0 < words; k0 += T * LOADS) {
         int32_t x[LOADS];
 #pragma unroll
@@ -656,17 +674,17 @@ __device__ __forceinline__ void stage_in(const int32_t *src, float *lat, int wor
     }
 }
 
-template <typename E, bool DEN, int LOADS>
+template <typename E, bool DEN, int LOADS, bool MANY = false>
 __device__ __forceinline__ void stage_out(E *W, const float *lat, const float *den, int words, int t, int T, int n,
-                                          int pitch)
+                                          int pitch, int apart = 0)
 {
-    Walk w(t, T, n, pitch);
+    Walk<MANY> w(t, T, n, pitch, apart);
     for (int k0 = t; k0 < words; k0 += T * LOADS) {
         float d[LOADS], x[LOADS];
 #pragma unroll
         for (int u = 0; u < LOADS; ++u) {
             const int k = k0 + u * T;
-            if constexpr (!DEN) d[u] = k < words ? den[k] : 0.0f;
+            if constexpr (!DEN) d[u] = k < words ? den[MANY ? w.unit() : k] : 0.0f;
             const int at = w.next();
             x[u] = k < words ? lat[at] : 0.0f;
         }
@@ -692,7 +710,7 @@ struct LatticePlan {
     int R[7], C[7];
 };
 
-template <typename E, bool DEN, int R>
+template <typename E, bool DEN, int R, bool MANY>
 __global__ __launch_bounds__(kBlurThreads) void k_lattice(const int32_t *__restrict__ cnt, E *__restrict__ W,
                                                  const float *__restrict__ den, int n, int r, int64_t f, int64_t v0,
                                                  LatticePlan lp, const uint32_t *__restrict__ flags)
@@ -705,9 +723,8 @@ __global__ __launch_bounds__(kBlurThreads) void k_lattice(const int32_t *__restr
     const int line = t % n, q = t / n;  // this thread's line and feature
     for (int64_t w0 = (int64_t)blockIdx.x * lp.per; w0 < f; w0 += (int64_t)gridDim.x * lp.per) {
         const int here = (int)(f - w0 < lp.per ? f - w0 : lp.per);
-        for (int p = 0; p < here; ++p)
-            stage_in<16>(cnt + (w0 + p) * M, lat + p * lp.words + lp.R[0] * lp.pitch + lp.C[0], M, t, threads, n,
-                         lp.pitch);
+        float *first = lat + lp.R[0] * lp.pitch + lp.C[0], *last = lat + lp.R[6] * lp.pitch + lp.C[6];
+        stage_in<MANY ? 8 : 16, MANY>(cnt + w0 * M, first, here * M, t, threads, n, lp.pitch, lp.words);
         __syncthreads();
         if (q < here) {
             float *a = lat + q * lp.words + line * lp.pitch;
@@ -727,9 +744,7 @@ __global__ __launch_bounds__(kBlurThreads) void k_lattice(const int32_t *__restr
                     line_pass(a + lp.R[s] * lp.pitch + lp.C[s], a + lp.R[s + 1] * lp.pitch + lp.C[s + 1], n, r, lp.pitch);
         }
         __syncthreads();
-        for (int p = 0; p < here; ++p)
-            stage_out<E, DEN, 8>(W + (v0 + w0 + p) * M, lat + p * lp.words + lp.R[6] * lp.pitch + lp.C[6], den, M, t,
-                                 threads, n, lp.pitch);
+        stage_out<E, DEN, 8, MANY>(W + (v0 + w0) * M, last, den, here * M, t, threads, n, lp.pitch, lp.words);
         __syncthreads();
     }
 }
@@ -956,6 +971,12 @@ void blur(const int32_t *cnt, float *a, float *b, float *out, int64_t f, int64_t
 
 constexpr int kLdsBytes = 160 * 1024;  // of a compute unit
 
+// Lattices of up to kManyEdge cells share workgroups, where half-widths past kManyRadius have no
+// windows in registers (a line of 21 r cells is too long), while there are kSpreadFeatures
+// features for each (36 x 36, 200 features: 50 us shared, 47 spread).
+constexpr int kManyEdge = 48, kManyRadius = 2, kSpreadFeatures = 512;
+static_assert(kManyEdge < 21 * (kManyRadius + 1), "see blur_plan");
+
 // How the blur runs at edge E and half-width r: whole lattices in LDS, lines in LDS, or
 // unit-major through memory. Measured per element of the field (fp32, blur and quotient,
 // 2e8 elements; through memory it takes 13-15 ps at large chunks, more at small ones):
@@ -996,7 +1017,11 @@ BlurPlan blur_plan(int64_t E, int64_t r)
         lp.C[s] = shift ? (s < 3 ? (3 - s) * d : 0) : (s & 1) * n;
         lp.R[s] = shift ? (s < 3 ? 3 : 6 - s) * d : 0;
     }
-    lp.per = n >= 64 ? 1 : 64 / n;
+    // Small lattices share a workgroup: its words are staged in one walk (lattice by lattice,
+    // 2 x 2 cells and 60,000 features took 156 us, now 43; 16 x 16 210 -> 105), and it takes as
+    // many lines as it has threads up to 20 cells, half as many up to 48 (32 x 32, r = 8: 248 and
+    // 211 us), one lattice from there on (63 x 63, r = 15: two 288, one 240).
+    lp.per = n <= kManyEdge ? kBlurThreads / (n <= 20 ? 1 : 2) / n : 1;
     const int64_t lds = (int64_t)lp.words * lp.per * 4;
     b.lattice = n <= kBlurThreads && (lds <= kLdsBytes / 2 || (lds <= kLdsBytes && 4 * r > n));
     b.line = small ? LinePlan{n, {0, 0, 0, 0}} : line_plan(E, r);
@@ -1046,7 +1071,14 @@ hipError_t allow_blur_lds(const BlurPlan &b, int64_t r)
     };
     return with_radius(b, r, [&](auto radius) {
         constexpr int R = decltype(radius)::value;
-        if (b.lattice) return allow(k_lattice<T, DEN, R>);
+        if (b.lattice) {
+            if constexpr (R <= kManyRadius)
+                if (b.lp.per > 1) {
+                    const hipError_t e = allow(k_lattice<T, DEN, R, true>);
+                    if (e != hipSuccess) return e;
+                }
+            return allow(k_lattice<T, DEN, R, false>);
+        }
         hipError_t e = allow(k_rows3<R>);
         if constexpr (R == 0)
             if (e == hipSuccess) e = allow(k_cols3<T, DEN>);
@@ -1067,9 +1099,18 @@ void blur_lds(const BlurPlan &b, const int32_t *cnt, float *rows, T *W, const fl
         constexpr int R = decltype(radius)::value;
         const dim3 block(kBlurThreads);
         if (b.lattice) {
-            const size_t lds = (size_t)b.lp.words * b.lp.per * 4;
-            hipLaunchKernelGGL((k_lattice<T, DEN, R>), grid((f + b.lp.per - 1) / b.lp.per), block, lds, st, cnt, W, den,
-                               n, rr, f, v0, b.lp, flags);
+            // few features are better spread over the chip than sharing workgroups
+            LatticePlan lp = b.lp;
+            if (lp.per > f / kSpreadFeatures) lp.per = f / kSpreadFeatures > 1 ? (int)(f / kSpreadFeatures) : 1;
+            const size_t lds = (size_t)lp.words * lp.per * 4;
+            const dim3 wgs = grid((f + lp.per - 1) / lp.per);
+            if constexpr (R <= kManyRadius)
+                if (lp.per > 1) {
+                    hipLaunchKernelGGL((k_lattice<T, DEN, R, true>), wgs, block, lds, st, cnt, W, den, n, rr, f, v0, lp,
+                                       flags);
+                    return;
+                }
+            hipLaunchKernelGGL((k_lattice<T, DEN, R, false>), wgs, block, lds, st, cnt, W, den, n, rr, f, v0, lp, flags);
             return;
         }
         const size_t row_lds = (size_t)b.row_lines * b.row_pitch * 4, col_lds = (size_t)b.col_lines * b.line.slots * 4;

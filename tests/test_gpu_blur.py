@@ -1,6 +1,6 @@
 """GPU parity of the update's blur at the sizes where its forms meet.
 
-A lattice is blurred whole in LDS (several features a workgroup below 64 cells, one up to
+A lattice is blurred whole in LDS (several features a workgroup up to 48 cells, one up to
 about 140), line by line in LDS up to about 1,000 cells, or through memory beyond; within
 LDS a pass writes d = min(r, E - 1) + 1 slots below its input or on the other half of its
 line, whichever is smaller. Edges and half-widths here lie on both sides of each line; the
@@ -26,6 +26,12 @@ pytestmark = pytest.mark.gpu
     (190, 1, 2, 3000, 0), (200, 5, 3, 9000, 1), (40, 4, 9, 900, 0),
     (41, 5, 9, 900, 0), (20, 6, 9, 900, 0), (201, 7, 2, 3000, 0), (202, 8, 2, 3000, 0), (203, 9, 2, 3000, 0),
     (5, 8, 9, 900, 0), (300, 2, 2, 9000, 0), (300, 6, 2, 9000, 0), (256, 3, 2, 9000, 0), (257, 128, 2, 9000, 0), (320, 40, 2, 9000, 0),
+    # lattices that share a workgroup (one for every 512 features), the last workgroup's share ragged, with and
+    # without places left out between them
+    (1, 2, 1100, 9000, 0), (2, 1, 70001, 9000, 0), (3, 2, 44003, 9000, 0), (5, 3, 27001, 9000, 0),
+    (12, 6, 11003, 9000, 0), (16, 8, 8203, 20000, 0), (20, 15, 6203, 20000, 0), (21, 1, 3100, 20000, 0),
+    (24, 2, 2777, 20000, 0), (33, 2, 1601, 20000, 0), (41, 2, 1603, 20000, 0), (48, 3, 1111, 20000, 0),
+    (48, 24, 1025, 20000, 400), (49, 24, 3, 900, 0),
     (515, 2, 1, 9000, 0), (600, 300, 1, 9000, 0), (700, 400, 1, 9000, 0), (1024, 1, 1, 9000, 0),
 ])
 def test_every_form_of_the_blur(dev, E, r, V, N, chunk, dtype):
