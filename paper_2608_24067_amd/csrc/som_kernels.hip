@@ -573,7 +573,6 @@ __global__ __launch_bounds__(256) void k_plan(const int32_t *__restrict__ off, i
 // A tile with more than kRankIds ids, an id outside [0, V), or a row that is not strictly
 // ascending takes plan_merge.
 constexpr int kRankIds = 512;
-constexpr int64_t kRankTiles = 16384, kRankTilesReal = 32768;  // see launch_plan
 
 // Orders a wave's LDS writes before the reads of its other lanes that follow.
 __device__ __forceinline__ void wave_sync()
@@ -1029,6 +1028,23 @@ hipError_t launch_check_rows(const int32_t *row_ptr, int64_t N, int64_t nnz, uin
     return hipGetLastError();
 }
 
+// Whether tiles of 8 are planned by ranks: their mean leaves room below kRankIds, and they are
+// few. The ranks take one wave and about 950 instructions a tile, the merge an eighth of a wave
+// for a dependent step per union entry (about 90 at 12 ids a row), so the merge wins once its
+// waves fill the chip, the sooner the shorter the rows; real-valued rows, whose merge also waits
+// for each value, later. Plan by ranks / by the merge, us, by rows: 1.9 ids a row 12.0 / 11.8 at
+// 60,000, 17.6 / 11.9 at 130,000; 3.6 ids 15.7 / 15.6 at 95,000; 11 ids 16.0 / 28.4 at 40,000, 29.4 /
+// 29.0 at 110,000; 20 ids 48.6 / 54.0 at 130,000. Real-valued: 1.9 ids 14.0 / 13.1 at 60,000; 3.6 ids
+// 21.9 / 21.3 at 110,000; 11 ids 41.0 / 44.4 at 130,000, 49.6 / 46.5 at 170,000; 20 ids 102 / 199 at
+// 260,000.
+static bool plan_by_ranks(int64_t N, int64_t nnz, int64_t nt, bool real)
+{
+    if (nnz * 8 > N * (kRankIds / 2)) return false;
+    if (nnz < 3 * N) return nt <= 6144;
+    if (!real) return nt <= (nnz < 16 * N ? 13312 : 16384);
+    return nt <= (nnz < 5 * N ? 13312 : (nnz < 16 * N ? 20480 : 32768));
+}
+
 hipError_t launch_plan(int ta, const int32_t *row_ptr, const int32_t *col_idx, const float *values, int64_t N,
                        int64_t nnz, int64_t V, const OrderBuffers *ob, uint2 *plan, int2 *tiles, float *vals,
                        double *xsq, uint32_t *flags, hipStream_t st)
@@ -1043,12 +1059,7 @@ hipError_t launch_plan(int ta, const int32_t *row_ptr, const int32_t *col_idx, c
     const int32_t *off = ob ? ob->pos : row_ptr;
     const int32_t *psrc = ob ? ob->pos + 1 : nullptr;
     const int os = ob ? 2 : 1;
-    // Tiles of 8 whose mean leaves room below kRankIds are planned by ranks while they are
-    // few: the ranks take one wave and about 950 instructions a tile, the merge an eighth of
-    // a wave for about 90 dependent steps, so the merge wins once its waves fill the chip
-    // (30,000 rows 27 -> 13 us by ranks, 300,000 rows 47 against 58, 2,000,000 167 against
-    // 388; real-valued rows, whose merge also waits for each value, 200,000 rows 70 -> 63).
-    if (ta == 8 && nnz * 8 <= N * (kRankIds / 2) && nt <= (xsq ? kRankTilesReal : kRankTiles)) {
+    if (ta == 8 && plan_by_ranks(N, nnz, nt, xsq != nullptr)) {
         int64_t rb = (nt + kPlanWaves - 1) / kPlanWaves;
         if (rb > (1 << 22)) rb = 1 << 22;
         if (xsq)  // real-valued rows (values is null when the batch holds no id)

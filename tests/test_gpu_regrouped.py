@@ -30,7 +30,7 @@ def batch(rules):
     rp[1:] = np.cumsum(lengths)
     ci = np.concatenate(pick).astype(np.int32)
     assert all(rules.regroups(N, M, len(ci), t) for t in (8, 16, 32))
-    assert len(ci) <= 32 * N and N <= 8 * 16384  # planned by ranks
+    assert 3 * N <= len(ci) <= 32 * N and N <= 8 * 13312  # planned by ranks
     W = synth.codebook(17, synth.QUANTISED, V, M)
     rows = np.unique(np.concatenate([rng.choice(N, 40), np.arange(0, N, 4 * LONG), [N - 1]]))
     return rp, ci, W, rows
