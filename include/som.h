@@ -96,8 +96,8 @@ typedef enum {
  * its BMU and distance do not depend on the tile it lands in.
  *   tile_samples  samples per tile, TA (SpMM-tile kernel section): 8, 16 or
  *                 32; 0 selects SOM_DEFAULT_TILE_SAMPLES.
- *   keep_order    0 (default): where it pays (large batches on maps of more
- *                 than 256 units), the plan first regroups the batch by each
+ *   keep_order    0 (default): where it pays (large batches; on maps of up
+ *                 to 256 units long rows only), the plan first regroups the batch by each
  *                 sample's least frequent feature (the post-submission
  *                 section's lever of clustering samples so tiles share
  *                 features), which shrinks tile unions and keeps rare

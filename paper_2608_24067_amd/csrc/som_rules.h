@@ -61,14 +61,17 @@ inline bool rows_direct(int64_t N, int64_t M, int64_t nnz, int ta, bool f16)
 // 256 x 256 491 / 446, 326 / 369, 183 / 339 at 2,000, 801 / 758, 490 / 600, 297 / 561 at 4,000;
 // 22 x 22 592 / 578, 462 / 576, 400 / 578 at 512,000. Longer rows gain as the product says (fp16
 // 64 x 64, 30,000 rows of 200 ids 1,984 / 2,502). Maps of up to 256 units, half a strip, read too
-// little per row (16 x 16, 2,000,000 rows 1,673 / 1,558, 1,534 / 1,555, 1,432 / 1,561).
+// little per row (16 x 16, 2,000,000 rows 1,673 / 1,558, 1,534 / 1,555, 1,432 / 1,561), unless the
+// rows are long and many (16 x 16, 80,000 rows of 110 ids 689 / 625, ten copies of each 388 / 616;
+// 5 x 5, fp16 712 / 638, 394 / 635; 20,000 rows 380 / 329).
 // fp16 sweeps gain less (64 x 64, 64,000 rows 365 / 337, 320 / 334, 276 / 334); the plan and the
 // finalize do not know the codebook's type. Nor do they know of a search that ran without a
 // plan: its workspace holds the rows in the order given, so wherever one may (an fp16 one, the
 // wider line) the phases regroup nothing.
 inline bool regroup_pays(int64_t N, int64_t M, int64_t nnz, int ta)
 {
-    return M > 256 && nnz * M >= (int64_t)9 << 28 && !rows_direct(N, M, nnz, ta, true);
+    const bool work = M > 256 ? nnz * M >= (int64_t)9 << 28 : nnz >= 48 * N && nnz >= (int64_t)5 << 20;
+    return work && !rows_direct(N, M, nnz, ta, true);
 }
 
 // Consecutive tiles per sweep workgroup. Longer groups let a wave keep its strip's

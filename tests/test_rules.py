@@ -47,7 +47,10 @@ def test_regrouping_covers_batches_whose_rows_may_resemble_each_other(rules):
     for N, M, ids in ((64000, 4096, 12), (16000, 16384, 12), (4000, 65536, 12), (8000, 65536, 12), (512000, 484, 12),
                       (30000, 4096, 200), (500000, 1 << 20, 12), (200, 1 << 20, 12)):
         assert rules.regroups(N, M, N * ids, 8), (N, M, ids)
-    for N, M, ids in ((32000, 4096, 12), (2000, 65536, 12), (2000000, 256, 12), (128000, 484, 12), (10000, 256, 12)):
+    for N, M, ids in ((85000, 25, 100), (300000, 256, 100)):  # long rows gain on the smallest maps too
+        assert rules.regroups(N, M, N * ids, 8), (N, M, ids)
+    for N, M, ids in ((32000, 4096, 12), (2000, 65536, 12), (2000000, 256, 12), (128000, 484, 12), (10000, 256, 12),
+                      (20000, 256, 100), (2000000, 256, 47)):
         assert not rules.regroups(N, M, N * ids, 8), (N, M, ids)
 
 
