@@ -995,7 +995,12 @@ template <typename E>
 static hipError_t norms_any(const E *W, int64_t V, int64_t M, double *norms, hipStream_t st)
 {
     const int64_t blocks = (M + 63) / 64;
-    if (blocks <= kNormFewBlocks)
+    // up to ten batches of 128 rows and a short rest are faster lane by lane: the pipeline's start
+    // is not worth it (4,096 units, pipeline / lanes, us: 128 rows 7.2 / 6.4, 512 10.5 / 7.5, 1,024
+    // 16.5 / 13.5; but 300 rows 8.2 / 9.1, 700 12.8 / 15.4, 30,000 rows 328 / 436), four batches of
+    // fp16 rows on more than 8,192 units (16,384 units, 512 rows 11.3 / 9.4, 1,024 17.6 / 18.9)
+    const bool batches = V >= 128 && V <= (sizeof(E) == 2 && blocks > 128 ? 512 + 27 : 1280) && V % 128 < 28;
+    if (blocks <= kNormFewBlocks && !batches)
         hipLaunchKernelGGL(k_norms_few<E>, dim3((unsigned)blocks), dim3(64 * (kNormProducers + 1)), 0, st, W, V, M,
                            norms);
     else if (blocks < kNormWavesFew)

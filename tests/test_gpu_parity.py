@@ -34,9 +34,11 @@ def test_norms_match_oracle_bitwise(dev, V, M, kind):
     assert np.array_equal(n_gpu, n_ref)
 
 
-# Maps of up to 16,384 units bring their rows in chunks of 112, three in flight; up to 32,704 a
-# lane reads 128 rows at a time, beyond that 32. Units and rows on both sides of each line.
-NORM_SHAPES = [(v, 130) for v in (1, 2, 111, 112, 113, 224, 335, 336, 337, 448, 449, 673)] + \
+# Maps of up to 16,384 units bring their rows in chunks of 112, three in flight (unless they are a
+# few whole batches of 128); up to 32,704 a lane reads 128 rows at a time, beyond that 32. Units and
+# rows on both sides of each line.
+NORM_SHAPES = [(v, 130) for v in (1, 2, 111, 112, 113, 127, 128, 155, 156, 224, 335, 336, 337, 448, 449, 673, 1280,
+                                  1307, 1308, 1408)] + \
               [(v, m) for v in (1, 31, 32, 33, 127, 128, 129, 300) for m in (16384, 16385, 32704, 32705, 40001)]
 
 
