@@ -836,7 +836,7 @@ __device__ __forceinline__ double row_length(const int32_t *row_ptr, int rs, int
 __global__ __launch_bounds__(64 * kFinalizeWaves) void k_finalize(
     const double *__restrict__ norms, int64_t M, const int32_t *__restrict__ row_ptr, int rs, int64_t N, int64_t nnz,
     FinalIn in, const double *__restrict__ xsq, const u64 *__restrict__ keys,
-    const float *__restrict__ dots, int64_t n_strips, FinalOut out)
+    const float *__restrict__ dots, int64_t n_strips, int64_t pitch, FinalOut out)
 {
     __shared__ u64 lk[kFinalizeWaves][64];
     __shared__ int ls[kFinalizeWaves][64];
@@ -853,7 +853,7 @@ __global__ __launch_bounds__(64 * kFinalizeWaves) void k_finalize(
                 u64 kk[kFinalizeBatch];
 #pragma unroll
                 for (int j = 0; j < kFinalizeBatch; ++j)
-                    kk[j] = g0 + j * waves < n_strips ? keys[(g0 + j * waves) * N + k] : kKeyNone;
+                    kk[j] = g0 + j * waves < n_strips ? keys[(g0 + j * waves) * pitch + k] : kKeyNone;
                 if (g0 == 0) kk[0] &= ~kKeyFlags;  // the flags that strip 0's key may carry
 #pragma unroll
                 for (int j = 0; j < kFinalizeBatch; ++j)
@@ -876,7 +876,7 @@ __global__ __launch_bounds__(64 * kFinalizeWaves) void k_finalize(
         if (y == 0 && k < N) {
             int64_t b = (int64_t)(best & kIndexMask);
             if (b >= M) b = M - 1;
-            out.put(k, (int32_t)b, fma(-2.0, (double)dots[gb * N + k], norms[b]) +
+            out.put(k, (int32_t)b, fma(-2.0, (double)dots[gb * pitch + k], norms[b]) +
                                        (xsq ? xsq[k] : row_length(row_ptr, rs, base, nnz, k)));
         }
         if (waves > 1) __syncthreads();
@@ -907,7 +907,7 @@ __global__ __launch_bounds__(64 * kFinalizeWaves) void k_finalize2(
     const double *__restrict__ norms, int64_t M, const int32_t *__restrict__ row_ptr, int rs, int64_t N, int64_t nnz,
     FinalIn in, const double *__restrict__ xsq, const u64 *__restrict__ keys,
     const float *__restrict__ dots, const u64 *__restrict__ keys2, const float *__restrict__ dots2, int64_t n_strips,
-    FinalOut out, FinalOut out2)
+    int64_t pitch, FinalOut out, FinalOut out2)
 {
     __shared__ TwoKeys lds[kFinalizeWaves][64];
     const int waves = (int)blockDim.y, y = (int)threadIdx.y;
@@ -924,7 +924,7 @@ __global__ __launch_bounds__(64 * kFinalizeWaves) void k_finalize2(
 #pragma unroll
                 for (int j = 0; j < kFinalize2Batch; ++j) {
                     const bool in = g0 + j * waves < n_strips;
-                    const int64_t at = (g0 + j * waves) * N + k;
+                    const int64_t at = (g0 + j * waves) * pitch + k;
                     k1[j] = in ? keys[at] : kKeyNone;
                     d1[j] = in ? dots[at] : 0.0f;
                     k2[j] = in ? keys2[at] : kKeyNone;
@@ -1103,7 +1103,9 @@ hipError_t launch_finalize(int ta, const double *norms, int64_t M, const int32_t
                            const OrderBuffers *ob, const double *xsq, const SweepOut &o, int32_t *bmu, double *dist,
                            int32_t *bmu2, double *dist2, hipStream_t st)
 {
-    const int64_t ns = n_strips(M, ta);
+    // rows without a plan fill strips of 512, each the first of two at tiles of 16 and 32
+    const bool wide = o.direct && ta != 8;
+    const int64_t ns = n_strips(M, wide ? 8 : ta), pitch = wide ? 2 * N : N;  // pitch: from a strip's keys to the next's
     const int waves = finalize_waves(ns);
     const dim3 block(waves > 1 ? 64 : 256, (unsigned)waves);
     int64_t blocks = (N + block.x - 1) / block.x;
@@ -1116,10 +1118,10 @@ hipError_t launch_finalize(int ta, const double *norms, int64_t M, const int32_t
     const FinalIn fin{o.flags, o.direct ? o.keys : nullptr, o.direct ? o.direct->flags : nullptr};
     if (bmu2)
         hipLaunchKernelGGL(k_finalize2, dim3((unsigned)blocks), block, 0, st, norms, M, rp, rs, N, nnz, fin, xsq,
-                           o.keys, o.dots, o.keys2, o.dots2, ns, o1, o2);
+                           o.keys, o.dots, o.keys2, o.dots2, ns, pitch, o1, o2);
     else
         hipLaunchKernelGGL(k_finalize, dim3((unsigned)blocks), block, 0, st, norms, M, rp, rs, N, nnz, fin, xsq,
-                           o.keys, o.dots, ns, o1);
+                           o.keys, o.dots, ns, pitch, o1);
     if (ob) {
         int64_t ub = (N + 255) / 256;
         if (ub > (1 << 22)) ub = 1 << 22;

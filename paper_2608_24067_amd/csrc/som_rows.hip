@@ -22,8 +22,11 @@
 namespace som {
 namespace {
 
-// kNpl: neurons per lane, as the workspace's keys are laid out (strips of 64 kNpl)
-template <typename E, int kNpl, int LD, bool TOP2, bool REAL>
+// Neurons per lane: strips of 512. Tiles of 16 and 32 lay the workspace's keys out in strips of
+// 256: a wave then fills the first of its two and leaves no key in the second.
+constexpr int kNpl = 8;
+
+template <typename E, int LD, bool TOP2, bool REAL>
 __global__ __launch_bounds__(64) void k_rows(const E *__restrict__ W, const double *__restrict__ norms, int64_t M,
                                              int64_t N, int64_t V, int64_t nnz, const int32_t *__restrict__ row_ptr,
                                              const int32_t *__restrict__ col_idx, const float *__restrict__ values,
@@ -33,7 +36,7 @@ __global__ __launch_bounds__(64) void k_rows(const E *__restrict__ W, const doub
                                              int2 *__restrict__ tiles, float *__restrict__ vals)
 {
     constexpr int G = group_elems<E, kNpl>();
-    constexpr int U = kNpl * sizeof(E) == 32 ? 8 : 16;  // codebook rows in flight: up to 64 registers
+    constexpr int U = sizeof(E) == 2 ? 16 : 8;  // codebook rows in flight: 64 registers
     typedef E vec __attribute__((ext_vector_type(G)));
     typedef vec any __attribute__((aligned(sizeof(E))));
     const int lane = threadIdx.x;
@@ -55,7 +58,7 @@ __global__ __launch_bounds__(64) void k_rows(const E *__restrict__ W, const doub
     const bool flagged = __ballot(bad) != 0;
     const int64_t rb = flagged ? 0 : row_ptr[row], re = flagged ? 0 : row_ptr[row + 1];
 
-    const int shift = kNpl == 8 ? 3 : (ta == 16 ? 4 : 5);  // 2^shift samples per tile
+    const int shift = ta == 8 ? 3 : (ta == 16 ? 4 : 5);  // 2^shift samples per tile
     const int slot = (int)row & ((1 << shift) - 1);
 
     double nrm[kNpl];
@@ -85,11 +88,6 @@ __global__ __launch_bounds__(64) void k_rows(const E *__restrict__ W, const doub
         const int left = __shfl(id, below ? 63 - __builtin_clzll(below) : 0);
         if (__ballot(in && id <= (below ? left : prev))) flag |= SOM_FLAG_UNSORTED;
         if (valid) prev = __builtin_amdgcn_readlane(id, 63 - __builtin_clzll(valid));
-        if (strip == 0 && lane < n) {
-            const int64_t at = p0 + lane - first;
-            plan[at] = make_uint2((unsigned)id, plan_word_one(1 << shift, slot, in));
-            if constexpr (REAL) vals[(at << shift) + slot] = x;
-        }
         for (int k = 0; k < n; k += U) {
             union {
                 vec v[U][kNpl / G];
@@ -122,6 +120,12 @@ __global__ __launch_bounds__(64) void k_rows(const E *__restrict__ W, const doub
                     acc[j] = REAL ? fmaf(xv, w, acc[j]) : acc[j] + w;
                 }
             }
+        }
+        // after the loads, which would wait for stores before them
+        if (strip == 0 && lane < n) {
+            const int64_t at = p0 + lane - first;
+            plan[at] = make_uint2((unsigned)id, plan_word_one(1 << shift, slot, in));
+            if constexpr (REAL) vals[(at << shift) + slot] = x;
         }
     }
 
@@ -168,9 +172,15 @@ __global__ __launch_bounds__(64) void k_rows(const E *__restrict__ W, const doub
     const u64 K1 = wave_min_u64(k1);
     const int o1 = owner_of(k1, K1);
     const float D1 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(q1), o1));
+    const int64_t at = (shift == 3 ? strip : 2 * strip) * N + row;
+    const bool second = shift != 3 && base + 32 * kNpl < Mi;  // the other strip of 256
     if (lane == 0) {
-        keys[strip * N + row] = strip == 0 ? (K1 & ~kKeyFlags) | (u64)flag << kKeyFlagShift : K1;
-        dots[strip * N + row] = D1;
+        keys[at] = strip == 0 ? (K1 & ~kKeyFlags) | (u64)flag << kKeyFlagShift : K1;
+        dots[at] = D1;
+        if (second) {
+            keys[at + N] = kKeyNone;
+            dots[at + N] = 0.0f;
+        }
     }
     if constexpr (TOP2) {
         const u64 nxt = lane == o1 ? k2 : k1;  // keys are distinct: each holds its neuron
@@ -178,8 +188,12 @@ __global__ __launch_bounds__(64) void k_rows(const E *__restrict__ W, const doub
         const u64 K2 = wave_min_u64(nxt);
         const float D2 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(nq), owner_of(nxt, K2)));
         if (lane == 0) {
-            keys2[strip * N + row] = K2;
-            dots2[strip * N + row] = D2;
+            keys2[at] = K2;
+            dots2[at] = D2;
+            if (second) {
+                keys2[at + N] = kKeyNone;
+                dots2[at + N] = 0.0f;
+            }
         }
     }
     if (strip == 0 && lane == 0) {
@@ -191,21 +205,21 @@ __global__ __launch_bounds__(64) void k_rows(const E *__restrict__ W, const doub
     }
 }
 
-template <typename E, int NPL, bool TOP2, bool REAL>
+template <typename E, bool TOP2, bool REAL>
 hipError_t rows_any(const void *w, const double *norms, int64_t M, int64_t N, int64_t V, int64_t nnz,
                     const SweepOut &o, hipStream_t st)
 {
     const E *W = static_cast<const E *>(w);
     const DirectRows &d = *o.direct;
-    const dim3 grid((unsigned)n_strips(M, d.ta), (unsigned)N);
+    const dim3 grid((unsigned)n_strips(M, 8), (unsigned)N);
     auto launch = [&](auto kernel) {
         hipLaunchKernelGGL(kernel, grid, dim3(64), 0, st, W, norms, M, N, V, nnz, d.row_ptr, d.col_idx, d.values,
                            o.keys, o.dots, o.keys2, o.dots2, d.xsq, d.ta, d.plan, d.tiles, d.vals);
     };
-    if (M >= group_elems<E, NPL>())
-        launch(k_rows<E, NPL, kLoadAny, TOP2, REAL>);
+    if (M >= group_elems<E, kNpl>())
+        launch(k_rows<E, kLoadAny, TOP2, REAL>);
     else
-        launch(k_rows<E, NPL, kLoadScalar, TOP2, REAL>);
+        launch(k_rows<E, kLoadScalar, TOP2, REAL>);
     return hipGetLastError();
 }
 
@@ -216,18 +230,15 @@ hipError_t launch_rows(bool f16, bool top2, const void *W, const double *norms, 
 {
     const bool real = o.direct->xsq != nullptr;
     if (real && o.direct->ta != 8) return hipErrorInvalidValue;
-    static_assert(neurons_per_lane(8) == 8 && neurons_per_lane(16) == 4 && neurons_per_lane(32) == 4,
-                  "the kernels below");
+    static_assert(neurons_per_lane(8) == kNpl && 2 * neurons_per_lane(16) == kNpl && 2 * neurons_per_lane(32) == kNpl,
+                  "the strips that a wave fills");
     auto pick = [&](auto e) {
         typedef decltype(e) E;
         if (real)
-            return top2 ? rows_any<E, 8, true, true>(W, norms, M, N, V, nnz, o, st)
-                        : rows_any<E, 8, false, true>(W, norms, M, N, V, nnz, o, st);
-        if (o.direct->ta == 8)
-            return top2 ? rows_any<E, 8, true, false>(W, norms, M, N, V, nnz, o, st)
-                        : rows_any<E, 8, false, false>(W, norms, M, N, V, nnz, o, st);
-        return top2 ? rows_any<E, 4, true, false>(W, norms, M, N, V, nnz, o, st)
-                    : rows_any<E, 4, false, false>(W, norms, M, N, V, nnz, o, st);
+            return top2 ? rows_any<E, true, true>(W, norms, M, N, V, nnz, o, st)
+                        : rows_any<E, false, true>(W, norms, M, N, V, nnz, o, st);
+        return top2 ? rows_any<E, true, false>(W, norms, M, N, V, nnz, o, st)
+                    : rows_any<E, false, false>(W, norms, M, N, V, nnz, o, st);
     };
     return f16 ? pick(_Float16{}) : pick(float{});
 }

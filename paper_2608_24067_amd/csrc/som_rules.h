@@ -70,7 +70,7 @@ inline bool rows_direct(int64_t N, int64_t M, int64_t nnz, int ta, bool f16)
 // wider line) the phases regroup nothing.
 inline bool regroup_pays(int64_t N, int64_t M, int64_t nnz, int ta)
 {
-    const bool work = M > 256 ? nnz * M >= (int64_t)9 << 28 : nnz >= 48 * N && nnz >= (int64_t)5 << 20;
+    const bool work = M > 256 ? nnz * M >= (int64_t)9 << 28 : ta == 8 && nnz >= 48 * N && nnz >= (int64_t)5 << 20;
     return work && !rows_direct(N, M, nnz, ta, true);
 }
 
