@@ -1041,10 +1041,13 @@ hipError_t launch_check_rows(const int32_t *row_ptr, int64_t N, int64_t nnz, uin
 // 60,000, 17.6 / 11.9 at 130,000; 3.6 ids 15.7 / 15.6 at 95,000; 11 ids 16.0 / 28.4 at 40,000, 29.4 /
 // 29.0 at 110,000; 20 ids 48.6 / 54.0 at 130,000. Real-valued: 1.9 ids 14.0 / 13.1 at 60,000; 3.6 ids
 // 21.9 / 21.3 at 110,000; 11 ids 41.0 / 44.4 at 130,000, 49.6 / 46.5 at 170,000; 20 ids 102 / 199 at
-// 260,000.
-static bool plan_by_ranks(int64_t N, int64_t nnz, int64_t nt, bool real)
+// 260,000. The merge reads a regrouped row lane by lane, the ranks read any row side by side
+// (plan with regrouping: 11 ids 70.5 / 69.6 at 130,000; 3.7 ids 108.7 / 108.0 at 110,000;
+// real-valued, 11 ids 102 / 109 at 200,000, 122 / 127 at 260,000).
+static bool plan_by_ranks(int64_t N, int64_t nnz, int64_t nt, bool real, bool regrouped)
 {
     if (nnz * 8 > N * (kRankIds / 2)) return false;
+    if (regrouped) return nt <= (nnz < 5 * N ? 13312 : (real ? 32768 : 16384));
     if (nnz < 3 * N) return nt <= 6144;
     if (!real) return nt <= (nnz < 16 * N ? 13312 : 16384);
     return nt <= (nnz < 5 * N ? 13312 : (nnz < 16 * N ? 20480 : 32768));
@@ -1064,7 +1067,7 @@ hipError_t launch_plan(int ta, const int32_t *row_ptr, const int32_t *col_idx, c
     const int32_t *off = ob ? ob->pos : row_ptr;
     const int32_t *psrc = ob ? ob->pos + 1 : nullptr;
     const int os = ob ? 2 : 1;
-    if (ta == 8 && plan_by_ranks(N, nnz, nt, xsq != nullptr)) {
+    if (ta == 8 && plan_by_ranks(N, nnz, nt, xsq != nullptr, ob != nullptr)) {
         int64_t rb = (nt + kPlanWaves - 1) / kPlanWaves;
         if (rb > (1 << 22)) rb = 1 << 22;
         if (xsq)  // real-valued rows (values is null when the batch holds no id)
