@@ -197,3 +197,38 @@ def test_update_residual_den_keeps_unreached_units(dev, f16):
     unreached = np.zeros((E, E), dtype=bool)
     unreached[6:, 5] = True
     assert np.array_equal(got[:, unreached.ravel()], W[:, unreached.ravel()])
+
+
+def test_updates_from_two_threads(dev):
+    """Two threads update lattices of different sizes through the same kernels, each on its own stream, codebook and
+    workspace: every result is the one the update gives alone."""
+    import threading
+
+    cases = []
+    for seed, E, r in ((121, 128, 64), (122, 64, 31)):
+        rp, ci, W, bmu = update_case(seed, 2000, 40, E)
+        want = gpu_update(W, rp, ci, bmu, E, r, dev)
+        args = [to_dev(x, dev) for x in (W, rp, ci, bmu)]
+        ws = torch.empty(som.update_workspace_bytes(40, E, 2000), dtype=torch.uint8, device=dev)
+        cases.append((E, r, args, ws, to_dev(want, dev)))
+    torch.cuda.synchronize()
+    wrong = []
+
+    def work(case):
+        E, r, (W, rp, ci, bmu), ws, want = case
+        try:
+            with torch.cuda.stream(torch.cuda.Stream()):
+                for _ in range(40):
+                    got = W.clone()
+                    som.update(got, rp, ci, bmu, 40, E, r, nnz=ci.numel(), workspace=ws)
+                    if not torch.equal(got, want):
+                        wrong.append(E)
+        except Exception as e:  # reported by the main thread
+            wrong.append(e)
+
+    threads = [threading.Thread(target=work, args=(c,)) for c in cases]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not wrong
